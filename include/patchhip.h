@@ -386,13 +386,16 @@ typedef struct {
                                  operands DMA'd into the wave's own LDS one
                                  chunk of four unknowns ahead; results equal
                                  the other two to roundoff);
-                                 1 = the wave-specialised stage kernel (one
-                                 work-group of 12 waves per CU: 8 waves stage
-                                 data and compute gradients while 4 run the
-                                 matrix product and the update; the default),
+                                 1 = the default: boxes of 128 cells, two
+                                 work-groups of 4 waves per CU, or, in batches
+                                 of no more 4x4x4 tiles than the device has
+                                 CUs, the wave-specialised kernel (12 waves
+                                 per CU: 8 stage data and compute gradients
+                                 while 4 run the matrix product and the
+                                 update),
                                  0 = the kernel in which every wave does every
-                                 phase (fd_wg_per_cu applies to it); both give
-                                 bitwise equal results */
+                                 phase (fd_wg_per_cu applies to it); 0 and 1
+                                 give bitwise equal results */
     int32_t fv_persist;       /* FV 3D, batches of one p (register kernel):
                                  w in 1..8 = a grid of w work-groups per CU,
                                  each marching an equal run of the batch's K*p

@@ -257,20 +257,15 @@ static pb_status enqueue_fd(pb_batch *b, double cfl, double dt_fixed, double sig
     }
     const double dt = fd_dt(b, cfl, dt_fixed);
     for (int i = 0; i < n; ++i) {
-        void *q0 = b->state[cur], *acc = b->state[cur ^ 1];
-        if (rk == 1) {
+        // stage 1 reads Q^n, stages 2-4 the previous stage value: y1 in the
+        // other state buffer (the last stage turns it into Q^(n+1) in place),
+        // y2 and y3 in the workspace
+        void *q0 = b->state[cur], *q1 = b->state[cur ^ 1];
+        void *yin[4] = {q0, q1, yA, yB}, *yout[4] = {q1, yA, yB, q1};
+        for (int sg = 0; sg < (rk == 1 ? 1 : 4); ++sg) {
             arm_events(b);
-            st = disarm_events(b, launch_fd_stage(b, 0, 1, q0, q0, nullptr, acc, dt, sigma, s));
+            st = disarm_events(b, launch_fd_stage(b, sg, rk, q0, yin[sg], q1, yA, yout[sg], dt, sigma, s));
             if (st != PB_OK) return st;
-        } else {
-            // stage 1 reads Q^n, stages 2-4 read the previous stage value
-            void *ys[4] = {q0, yA, yB, yA};
-            void *yn[4] = {yA, yB, yA, nullptr};
-            for (int sg = 0; sg < 4; ++sg) {
-                arm_events(b);
-                st = disarm_events(b, launch_fd_stage(b, sg, 4, q0, ys[sg], yn[sg], acc, dt, sigma, s));
-                if (st != PB_OK) return st;
-            }
         }
         cur ^= 1;
     }
@@ -395,10 +390,7 @@ pb_status patch_batch_destroy(pb_batch *b)
         for (auto ev : b->prof_ev[w]) (void)hipEventDestroy(ev);
     if (b->capture_stream) (void)hipStreamDestroy(b->capture_stream);
     (void)hipFree(b->d_patches);
-    if (b->d_fd_items) (void)hipFree(b->d_fd_items);
-    if (b->d_fd_ws_items) (void)hipFree(b->d_fd_ws_items);
-    if (b->d_fd_B) (void)hipFree(b->d_fd_B);
-    if (b->d_fd_A) (void)hipFree(b->d_fd_A);
+    if (b->d_fd_mem) (void)hipFree(b->d_fd_mem);
     if (b->fv_runs.d) (void)hipFree(b->fv_runs.d);
     if (b->fd_runs.d) (void)hipFree(b->fd_runs.d);
     delete b;

@@ -266,9 +266,13 @@ struct pb_batch {
     bool pres_valid = false;         // SRHD: the workspace holds a previous pressure
     // FD: tile work list (largest patches first) and the B_d matrices
     bool fd_ready = false;
+    void *d_fd_mem = nullptr;        // one allocation that holds every table below
     void *d_fd_items = nullptr;
     void *d_fd_ws_items = nullptr;   // per-tile geometry of the wave-specialised kernel
     int fd_n_items = 0;
+    void *d_fd_boxes = nullptr;      // 128-cell boxes of the box kernel
+    int fd_n_boxes = 0;
+    void *d_fd_boxA = nullptr;       // A operands of the box kernel
     double *d_fd_B = nullptr;
     double *d_fd_A = nullptr;        // A operands of the one-wave-per-tile FD kernel
     // graph cache
@@ -339,8 +343,11 @@ pb_status launch_fv_step(pb_batch *b, const void *qin, void *qout, int slot_in, 
                          double cfl, hipStream_t s);
 pb_status launch_srhd_c2p(pb_batch *b, const void *q, int slot_out, bool want_dt, double cfl,
                           hipStream_t s);
-pb_status launch_fd_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y,
-                          void *ynext, void *acc, double dt, double sigma, hipStream_t s);
+// one stage of the linear system's step: `out` from Q0 and the stage input y
+// (stage 0: Q0 itself); the last RK4 stage also reads the earlier stages'
+// values y1 and y2, and out may be y1
+pb_status launch_fd_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, const void *y1,
+                          const void *y2, void *out, double dt, double sigma, hipStream_t s);
 // one stage of the Euler FD4 + KO6 step (dt from ctrl->dt[slot] unless
 // dt_fixed > 0; the last stage writes the next step's dt to slot ^ 1)
 pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, void *ynext,

@@ -5,10 +5,12 @@
 //   D4 u  = [(u_-2 - u_+2) + 8 (u_+1 - u_-1)] / (12 dx),
 //   KO6 u = sigma/(64 dx) [(u_-3 + u_+3) - 6 (u_-2 + u_+2) + 15 (u_-1 + u_+1) - 20 u_0].
 //
-// Two kernels compute the same stage with the same arithmetic in the same
+// Three kernels compute the same stage with the same arithmetic in the same
 // order (bitwise equal results): fd_stage_kernel below, in which every wave
-// runs every phase, and fd_stage_ws_kernel further down (the default), which
-// splits the phases between producer and consumer waves.
+// runs every phase; fd_stage_ws_kernel, which splits the phases between
+// producer and consumer waves (the default for batches of no more 4x4x4 tiles
+// than the chip has CUs); and fd_stage_box_kernel further down (the default
+// for every larger batch).
 //
 // Work decomposition of fd_stage_kernel (MI355X): one persistent launch per
 // RK stage, two work-groups of four waves per CU.  Work items are 4x4x4 cell tiles, listed
@@ -48,6 +50,8 @@
 // memory clobber so no LDS access moves across it.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "pb_common.h"
@@ -160,6 +164,17 @@ __device__ __forceinline__ void barrier_keep(int pending)
     __asm__ volatile("s_barrier" ::: "memory");
 }
 
+// Classical RK4 with stage values y1 = Q0 + dt/2 k1, y2 = Q0 + dt/2 k2,
+// y3 = Q0 + dt k3 and no running sum of the k: the new state is
+//   Q0 + ((y1 - Q0) + 2 (y2 - Q0) + (y3 - Q0)) / 3 + dt/6 k4,
+// so stages 1-3 read Q0 and write one array each, and only the last stage
+// reads y1, y2 and its own y3: 13 passes over the state per step instead of
+// the 16 of a running sum, with two roundings of the sum instead of four.
+__device__ __forceinline__ double rk_base(double q0, double y1, double y2, double y3)
+{
+    return q0 + ((y1 - q0) + 2.0 * (y2 - q0) + (y3 - q0)) * (1.0 / 3.0);
+}
+
 // LDS writes done, then the work-group barrier
 __device__ __forceinline__ void barrier_lds()
 {
@@ -169,11 +184,12 @@ __device__ __forceinline__ void barrier_lds()
 
 }  // namespace
 
-// stage: 0..3 (RK4) with rk = 4, or 0 with rk = 1
+// One stage: out = base + ca R(y), see rk_base (fin: the last stage of RK4).
+// out may be y1 (each element is read by the thread that writes it).
 __global__ __launch_bounds__(kFdThreads, 2) void fd_stage_kernel(
-    const double *__restrict__ y, const double *__restrict__ q0, double *__restrict__ ynext,
-    double *__restrict__ acc, const PatchDev *__restrict__ patches, const FdItem *__restrict__ items, int n_items,
-    const double *__restrict__ Bmat, int N, int stage, int rk, double dt, double sigma, int remap)
+    const double *__restrict__ y, const double *__restrict__ q0, const double *y1, const double *__restrict__ y2,
+    double *out, const PatchDev *__restrict__ patches, const FdItem *__restrict__ items, int n_items,
+    const double *__restrict__ Bmat, int N, int fin, double ca, double sigma, int remap)
 {
     __shared__ double sQ0[kCh][kFoot], sQ1[kCh][kFoot];
     __shared__ double sG[3][kCh][kTC];
@@ -296,24 +312,23 @@ __global__ __launch_bounds__(kFdThreads, 2) void fd_stage_kernel(
             // 3. accumulate -B_d G_d over the chunk's K rows on the matrix cores
             if (v0 < N) {
 #pragma unroll
-                for (int d = 0; d < 3; ++d)
+                for (int kk = 0; kk < kCh / 4; ++kk) {
+                    const int ks = ch * (kCh / 4) + kk;
+                    if (ks >= kMaxN / 4) break;
 #pragma unroll
-                    for (int kk = 0; kk < kCh / 4; ++kk) {
-                        const int ks = ch * (kCh / 4) + kk;
-                        if (ks >= kMaxN / 4) break;
+                    for (int d = 0; d < 3; ++d) {
                         const double aop = a[d][ks];
 #pragma unroll
                         for (int nt = 0; nt < 4; ++nt)
                             accm[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(aop, sG[d][4 * kk + lg][nt * 16 + lj],
                                                                             accm[nt], 0, 0, 0);
                     }
-                // the wave whose output rows are this chunk's unknowns adds KO6
-                if (w == ch / 2) {
-                    const int h = ch % 2;
+                    // the wave whose output rows are these unknowns adds their KO6
+                    if (w == ch / 2) {
 #pragma unroll
-                    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                        for (int ii = 0; ii < 2; ++ii) accm[nt][2 * h + ii] += sK[lg + 4 * ii][nt * 16 + lj];
+                        for (int nt = 0; nt < 4; ++nt)
+                            accm[nt][2 * (ch % 2) + kk] += sK[lg + 4 * kk][nt * 16 + lj];
+                    }
                 }
             }
         }
@@ -321,11 +336,10 @@ __global__ __launch_bounds__(kFdThreads, 2) void fd_stage_kernel(
         //    tiles: all reads of a round first (one memory round trip), then
         //    the arithmetic and the stores
         {
-            const bool need_q0 = rk == 1 || stage < 3, need_acc = rk == 4 && stage > 0;
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 long long gbase[2];
-                double q0v[2][4], accv[2][4];
+                double bv[2][4];
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int c = (2 * half + h) * 16 + lj;
@@ -338,31 +352,15 @@ __global__ __launch_bounds__(kFdThreads, 2) void fd_stage_kernel(
                     for (int i = 0; i < 4; ++i) {
                         const int r = 16 * w + lg + 4 * i;
                         const long long g = gbase[h] + (long long)(r < N ? r : 0) * C;
-                        q0v[h][i] = (r < N && need_q0) ? q0[g] : 0.0;
-                        accv[h][i] = (r < N && need_acc) ? acc[g] : 0.0;
+                        bv[h][i] = q0[g];
+                        if (fin) bv[h][i] = rk_base(bv[h][i], y1[g], y2[g], y[g]);
                     }
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const int r = 16 * w + lg + 4 * i;
-                        if (r >= N) continue;
-                        const long long g = gbase[h] + (long long)r * C;
-                        const double R = accm[2 * half + h][i];
-                        if (rk == 1) {
-                            acc[g] = q0v[h][i] + dt * R;
-                        } else if (stage == 0) {
-                            ynext[g] = q0v[h][i] + 0.5 * dt * R;
-                            acc[g] = q0v[h][i] + (dt / 6.0) * R;
-                        } else if (stage == 1) {
-                            ynext[g] = q0v[h][i] + 0.5 * dt * R;
-                            acc[g] = accv[h][i] + (dt / 3.0) * R;
-                        } else if (stage == 2) {
-                            ynext[g] = q0v[h][i] + dt * R;
-                            acc[g] = accv[h][i] + (dt / 3.0) * R;
-                        } else {
-                            acc[g] = accv[h][i] + (dt / 6.0) * R;
-                        }
+                        if (r < N) out[gbase[h] + (long long)r * C] = bv[h][i] + ca * accm[2 * half + h][i];
                     }
             }
         }
@@ -449,14 +447,19 @@ struct WsLds {
     double q[2][kCh][kFoot];             // footprint ring
     double g[2][3][kCh][kTC];            // gradients (matrix-core B operands)
     double k[2][kCh][kTC];               // summed dissipation
-    double u[R][2][kCh][kTC];            // update operands: [slot][Q^0-side, acc-side][unknown][cell]
+    double u[R][kCh][kTC];               // update operand (what the stage adds its ca R to): [slot][unknown][cell]
+};
+
+// what a producer loads for one cell's update (y1, y2, y3: the last stage of RK4)
+struct Upd {
+    double q = 0.0, y1 = 0.0, y2 = 0.0, y3 = 0.0;
 };
 
 // producer waves: footprints, gradients and dissipation, update operands
 template <int NCH>
 __device__ __forceinline__ void ws_producer(WsLds<NCH> &L, const double *__restrict__ y,
-                                            const double *__restrict__ srcq, const double *__restrict__ srca,
-                                            double *__restrict__ acc, double *__restrict__ ynext, bool write_y,
+                                            const double *__restrict__ q0, const double *y1,
+                                            const double *__restrict__ y2, double *out, bool fin,
                                             const WsItem *__restrict__ items, int slot, int G, int S, int N,
                                             double sigma)
 {
@@ -475,11 +478,10 @@ __device__ __forceinline__ void ws_producer(WsLds<NCH> &L, const double *__restr
         sz[k] = foot_slot(cx, cy, cz - 3 + k);
         sz[3 + k] = foot_slot(cx, cy, cz + 1 + k);
     }
-    // this thread's piece of the update operands of a chunk: side (Q^0 or
-    // accumulator), unknown within the chunk, two x-adjacent cells
-    const int us = t >> 8, uv = (t >> 5) & 7, uc = 2 * (t & 31);
+    // this thread's piece of the update operands of a chunk: one cell of the
+    // unknown pw within the chunk
+    const int uv = pw, uc = l;
     const int ux = uc % kT, uy = (uc / kT) % kT, uz = uc / (kT * kT);
-    const double *__restrict__ usrc = us ? srca : srcq;
     // tile caches of the three cursors (footprint loads, gradients, operand loads)
     int kf = -1, kg = -1, ku = -1, ko = -1;
     TileSrc fsrc{};
@@ -502,7 +504,7 @@ __device__ __forceinline__ void ws_producer(WsLds<NCH> &L, const double *__restr
 #pragma unroll
         for (int i = 0; i < 3; ++i) *reinterpret_cast<f64x2_t *>(&L.q[b][pw][128 * i + 2 * l]) = F[i];
     };
-    auto load_upd = [&](int c) -> f64x2_t {
+    auto load_upd = [&](int c) -> Upd {
         c = c < S ? c : S - 1;
         const int k = c / NCH, ch = c - k * NCH;
         if (k != ku) {
@@ -514,14 +516,21 @@ __device__ __forceinline__ void ws_producer(WsLds<NCH> &L, const double *__restr
         }
         const int v0 = ch * kCh + uv, v = v0 < N ? v0 : N - 1;
         // v < 64 and uC = p^3 <= 4096: a 24-bit product
-        return *reinterpret_cast<const f64x2_t *>(usrc + ubase + __umul24((unsigned)v, (unsigned)uC));
+        const long long g = ubase + __umul24((unsigned)v, (unsigned)uC);
+        Upd U;
+        U.q = q0[g];
+        if (fin) {
+            U.y1 = y1[g];
+            U.y2 = y2[g];
+            U.y3 = y[g];
+        }
+        return U;
     };
-    auto stage_upd = [&](int c, const f64x2_t &U) {
-        if (c < S) *reinterpret_cast<f64x2_t *>(&L.u[c % R][us][uv][uc]) = U;
+    auto stage_upd = [&](int c, const Upd &U) {
+        if (c < S) L.u[c % R][uv][uc] = fin ? rk_base(U.q, U.y1, U.y2, U.y3) : U.q;
     };
     // the stage results of chunk c (written into its ring slot by the
-    // consumers at the tile's last step) to HBM: new accumulator (side 0)
-    // and next stage value (side 1, where the stage has one)
+    // consumers at the tile's last step) to HBM
     auto store_out = [&](int c) {
         if (c < 0) return;
         const int k = c / NCH, ch = c - k * NCH;
@@ -533,11 +542,7 @@ __device__ __forceinline__ void ws_producer(WsLds<NCH> &L, const double *__restr
             obase = T.off * N + ((long long)(T.tz + uz) * p + (T.ty + uy)) * p + (T.tx + ux);
         }
         const int v = ch * kCh + uv;
-        if (v < N && (us == 0 || write_y)) {
-            const f64x2_t r = *reinterpret_cast<const f64x2_t *>(&L.u[c % R][us][uv][uc]);
-            double *dst = us ? ynext : acc;
-            *reinterpret_cast<f64x2_t *>(dst + obase + __umul24((unsigned)v, (unsigned)oC)) = r;
-        }
+        if (v < N) out[obase + __umul24((unsigned)v, (unsigned)oC)] = L.u[c % R][uv][uc];
     };
     auto grad = [&](int c) {
         c = c < S ? c : S - 1;
@@ -580,7 +585,8 @@ __device__ __forceinline__ void ws_producer(WsLds<NCH> &L, const double *__restr
     // step -2 and -1 (before the consumers' first product), then steps 0..S-1;
     // footprint sets: FA for even steps, FB for odd; operand sets: UB for
     // even steps, UA for odd
-    f64x2_t FA[3], FB[3], UA, UB;
+    f64x2_t FA[3], FB[3];
+    Upd UA, UB;
     load_foot(0, FA);
     load_foot(1, FB);
     UA = load_upd(0);
@@ -624,7 +630,7 @@ __device__ __forceinline__ void ws_producer(WsLds<NCH> &L, const double *__restr
 template <int NCH>
 __device__ __forceinline__ void ws_consumer(WsLds<NCH> &L, const WsItem *__restrict__ items, int slot, int G,
                                             int n_my,
-                                            const double *__restrict__ Bmat, int N, int stage, int rk, double dt)
+                                            const double *__restrict__ Bmat, int N, double ca)
 {
     constexpr int R = WsLds<NCH>::R;
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, lg = l >> 4, lj = l & 15;
@@ -641,13 +647,6 @@ __device__ __forceinline__ void ws_consumer(WsLds<NCH> &L, const WsItem *__restr
                 a[d][ks] = (m < N && k < N) ? -bv : 0.0;
             }
     }
-    // the stage update, with one form for every stage:
-    //   acc <- (Q^0-side) + ca R,   ynext <- Q^0 + cy R (stages 1-3 of RK4);
-    // the operand ring holds Q^0 (or, where a stage needs no Q^0, the
-    // accumulator) on one side and the accumulator (or Q^0) on the other
-    const bool from_q0 = !(rk == 4 && stage > 0);
-    const double ca = rk == 1 ? dt : ((stage == 0 || stage == 3) ? dt / 6.0 : dt / 3.0);
-    const double cy = stage == 2 ? dt : 0.5 * dt;
     lds_barrier();
     lds_barrier();
     int s = 0;
@@ -659,23 +658,22 @@ __device__ __forceinline__ void ws_consumer(WsLds<NCH> &L, const WsItem *__restr
         for (int ch = 0; ch < NCH; ++ch, ++s) {
             const int b = s & 1;
 #pragma unroll
-            for (int d = 0; d < 3; ++d)
+            for (int kk = 0; kk < kCh / 4; ++kk) {
+                const int ks = ch * (kCh / 4) + kk;
+                if (ks >= kMaxN / 4) break;
 #pragma unroll
-                for (int kk = 0; kk < kCh / 4; ++kk) {
-                    const int ks = ch * (kCh / 4) + kk;
-                    if (ks >= kMaxN / 4) break;
+                for (int d = 0; d < 3; ++d) {
                     const double aop = a[d][ks];
 #pragma unroll
                     for (int nt = 0; nt < 4; ++nt)
                         accm[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(aop, L.g[b][d][4 * kk + lg][nt * 16 + lj],
                                                                         accm[nt], 0, 0, 0);
                 }
-            if (w == ch / 2) {
-                const int h = ch % 2;
+                if (w == ch / 2) {
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                    for (int ii = 0; ii < 2; ++ii) accm[nt][2 * h + ii] += L.k[b][lg + 4 * ii][nt * 16 + lj];
+                    for (int nt = 0; nt < 4; ++nt)
+                        accm[nt][2 * (ch % 2) + kk] += L.k[b][lg + 4 * kk][nt * 16 + lj];
+                }
             }
             if (ch == NCH - 1) {
                 // element (nt, i) of this lane: unknown r = 16 w + lg + 4 i,
@@ -683,22 +681,18 @@ __device__ __forceinline__ void ws_consumer(WsLds<NCH> &L, const WsItem *__restr
                 // operands in the ring slot (the producers write them to HBM
                 // over the next tile's steps); rows at or beyond N are
                 // skipped (beyond the last chunk a row would alias one of it)
-                double *ul = &L.u[0][0][lg][lj];
+                double *ul = &L.u[0][lg][lj];
                 const int c0 = s - ch;   // global index of the tile's first chunk
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     // operand ring slot of unknown row r (its chunk is 2 w + i / 2)
                     const int rc = 2 * w + i / 2 < NCH ? 2 * w + i / 2 : NCH - 1;
-                    double *ui = ul + ((c0 + rc) % R) * (2 * kCh * kTC) + 4 * (i % 2) * kTC;
+                    double *ui = ul + ((c0 + rc) % R) * (kCh * kTC) + 4 * (i % 2) * kTC;
                     const bool live = 16 * w + lg + 4 * i < N;
 #pragma unroll
                     for (int nt = 0; nt < 4; ++nt) {
-                        const double R0 = accm[nt][i], qv = ui[nt * 16], av = ui[kCh * kTC + nt * 16];
-                        const double an = (from_q0 ? qv : av) + ca * R0, yn = qv + cy * R0;
-                        if (live) {
-                            ui[nt * 16] = an;
-                            ui[kCh * kTC + nt * 16] = yn;
-                        }
+                        const double v = ui[nt * 16] + ca * accm[nt][i];
+                        if (live) ui[nt * 16] = v;
                     }
                 }
             }
@@ -711,22 +705,18 @@ __device__ __forceinline__ void ws_consumer(WsLds<NCH> &L, const WsItem *__restr
 
 template <int NCH>
 __global__ __launch_bounds__(kWsThreads) void fd_stage_ws_kernel(
-    const double *__restrict__ y, const double *__restrict__ q0, double *__restrict__ ynext,
-    double *__restrict__ acc, const WsItem *__restrict__ items, int n_items, const double *__restrict__ Bmat, int N,
-    int stage, int rk, double dt, double sigma, int remap)
+    const double *__restrict__ y, const double *__restrict__ q0, const double *y1, const double *__restrict__ y2,
+    double *out, const WsItem *__restrict__ items, int n_items, const double *__restrict__ Bmat, int N, int fin,
+    double ca, double sigma, int remap)
 {
     __shared__ WsLds<NCH> L;
     const int G = (int)gridDim.x, slot = remap ? xcd_remap((int)blockIdx.x, G) : (int)blockIdx.x;
     if (slot >= n_items) return;
     const int n_my = (n_items - slot + G - 1) / G;
     if (threadIdx.x >= 256) {
-        // the stage's update operands: Q^0 and the accumulator where it needs
-        // both, else the one it needs on both sides
-        const bool need_q0 = rk == 1 || stage < 3, need_acc = rk == 4 && stage > 0;
-        ws_producer<NCH>(L, y, need_q0 ? q0 : acc, need_acc ? acc : q0, acc, ynext, rk == 4 && stage < 3, items,
-                         slot, G, n_my * NCH, N, sigma);
+        ws_producer<NCH>(L, y, q0, y1, y2, out, fin != 0, items, slot, G, n_my * NCH, N, sigma);
     } else {
-        ws_consumer<NCH>(L, items, slot, G, n_my, Bmat, N, stage, rk, dt);
+        ws_consumer<NCH>(L, items, slot, G, n_my, Bmat, N, ca);
     }
 }
 
@@ -798,9 +788,9 @@ __device__ __forceinline__ void tile_wait_all()
 }
 
 __global__ __launch_bounds__(64) void fd_stage_tile_kernel(
-    const double *__restrict__ y, const double *__restrict__ q0, double *__restrict__ ynext,
-    double *__restrict__ acc, const WsItem *__restrict__ items, int n_items, const double *__restrict__ apk,
-    int N, int stage, int rk, double dt, double sigma, int remap)
+    const double *__restrict__ y, const double *__restrict__ q0, const double *y1, const double *__restrict__ y2,
+    double *out, const WsItem *__restrict__ items, int n_items, const double *__restrict__ apk, int N, int fin,
+    double ca, double sigma, int remap)
 {
     __shared__ TileLds L;
     const int l = threadIdx.x, g = l >> 4, j = l & 15;
@@ -824,7 +814,6 @@ __global__ __launch_bounds__(64) void fd_stage_tile_kernel(
             ystr[k] = 24;
         }
     }
-    const bool need_q0 = rk == 1 || stage < 3, need_acc = rk == 4 && stage > 0;
     int buf = 0;
     for (int it = slot; it < n_items; it += G) {
         const WsItem W = items[it];
@@ -912,15 +901,16 @@ __global__ __launch_bounds__(64) void fd_stage_tile_kernel(
         const long long cell = ((long long)W.tz * p + (W.ty + yy)) * p + (W.tx + x);
 #pragma unroll
         for (int rt = 0; rt < 4; ++rt) {
-            double qv[4][4], av[4][4];
+            double bv[4][4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int r = 16 * rt + 4 * i + g;
                 const long long gr = W.off * N + (long long)(r < N ? r : 0) * C + cell;
 #pragma unroll
                 for (int nt = 0; nt < 4; ++nt) {
-                    qv[i][nt] = (r < N && need_q0) ? q0[gr + nt * pp] : 0.0;
-                    av[i][nt] = (r < N && need_acc) ? acc[gr + nt * pp] : 0.0;
+                    const long long gi = gr + nt * pp;
+                    bv[i][nt] = q0[gi];
+                    if (fin) bv[i][nt] = rk_base(bv[i][nt], y1[gi], y2[gi], y[gi]);
                 }
             }
 #pragma unroll
@@ -929,26 +919,385 @@ __global__ __launch_bounds__(64) void fd_stage_tile_kernel(
                 if (r >= N) continue;
                 const long long gr = W.off * N + (long long)r * C + cell;
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt) {
-                    const long long gi = gr + nt * pp;
-                    const double R = am[rt][nt][i];
-                    if (rk == 1) {
-                        acc[gi] = qv[i][nt] + dt * R;
-                    } else if (stage == 0) {
-                        ynext[gi] = qv[i][nt] + 0.5 * dt * R;
-                        acc[gi] = qv[i][nt] + (dt / 6.0) * R;
-                    } else if (stage == 1) {
-                        ynext[gi] = qv[i][nt] + 0.5 * dt * R;
-                        acc[gi] = av[i][nt] + (dt / 3.0) * R;
-                    } else if (stage == 2) {
-                        ynext[gi] = qv[i][nt] + dt * R;
-                        acc[gi] = av[i][nt] + (dt / 3.0) * R;
-                    } else {
-                        acc[gi] = av[i][nt] + (dt / 6.0) * R;
-                    }
-                }
+                for (int nt = 0; nt < 4; ++nt) out[gr + nt * pp] = bv[i][nt] + ca * am[rt][nt][i];
             }
         }
+    }
+}
+
+// ------------------------------------------------------- boxes of 128 cells --
+//
+// Two independent work-groups of four waves per CU (two waves per SIMD, one of
+// each) advance boxes of 128 cells: 16 cells along x, 4 along y, 2 along z.
+// Along x a box holds a whole period: one row of a 16^3 patch, or the rows of
+// two 8^3 or four 4^3 patches side by side, so x needs no halo and every
+// footprint row is 16 doubles.  The footprint of an unknown is 44 such rows:
+// the 2 planes of the box with 3 rows below and above in y (20 rows), and the
+// 3 planes below and above in z (24 rows).
+//
+// Unknowns go in chunks of four, one K step of v_mfma_f64_16x16x4f64.  Wave w
+// owns the box rows (y, z) = (2 (w % 2) + {0, 1}, w / 2): two column tiles of
+// 16 cells and all 16 RT output rows (accumulators: 64 registers).  Lane l
+// differentiates unknown 4 c + l / 16 at cell x = l % 16 of its two rows: its
+// three D4 values are the matrix instruction's B operands, and its KO6 value
+// belongs to the lane's own accumulator register (c % 4) of row tile c / 4.
+// Nothing goes from wave to wave but the footprint.  The A operands (-B_d)
+// come from a packed 90 KB table that stays in L2 (6 KB per chunk, which the
+// four waves read at about the same time).
+//
+// Step s of the flattened sequence (box, chunk), one barrier each:
+//   - the footprint of step s + 1 goes from registers to the other of two LDS
+//     buffers (all reads of it ended with step s - 1), and the loads of step
+//     s + 2 go out into the same registers;
+//   - the stencil values of step s are read from LDS, and the matrix
+//     instructions of step s - 1 run in one block while they arrive; then the
+//     arithmetic.  Matrix and vector instructions are kept in blocks: on this
+//     chip an FP64 matrix instruction (64 cycles) holds the SIMD's whole vector
+//     unit, 32-bit instructions and the other wave's included, and every change
+//     from one to the other costs about 7 cycles more (24 matrix and 72 vector
+//     instructions of each of two waves: 3722 cycles in two blocks, 4051 with
+//     three vector instructions after every matrix one);
+//   - after a box's last chunk the stage update in the accumulators' layout,
+//     while the CU's other work-group computes.
+// The chunk loop is unrolled, so that chunk c's KO6 is a fixed register.
+// The additions run in the other kernels' order (K steps in order, directions
+// within one, then that chunk's KO6), so all of them agree bitwise.
+//
+// Bound: the vector unit.  Per box and SIMD, 15 chunks of 24 matrix and about
+// 82 vector instructions: 29 k cycles for 58 unknowns, 2.0 ms per stage of the
+// batch of 4096 uneven patches (5.3 M cells); its 13 passes over the state per
+// step are 1.3 ms per stage at the copy rate.  Measured on that batch, per
+// step: 13.0 ms (stages 1-3 3.2 ms, the last 3.85 ms) against 19.2 ms with
+// fd_stage_ws_kernel and a running sum.  Of the difference to the bound, the
+// updates are about 0.5 ms per stage, the operand loads 0.15, the footprint
+// traffic 0.3 (variants without each).  Tried: boxes of 256 cells, one
+// work-group of eight waves per CU with the A operands in LDS: 3.0 ms of a
+// 13.6 ms step were the updates, with every wave of the chip in the same
+// phase.
+constexpr int kBoxThreads = 256;
+constexpr int kBoxZ = 2;                         // planes of a box
+constexpr int kBoxOwn = 10 * kBoxZ;              // rows of its own planes (with the y halo)
+constexpr int kBoxRows = 48;                     // 44 and four repeated ones: 6 pieces per thread and chunk
+// LDS of the two footprint buffers, row by row: row r of buffer b of unknown u
+// at u * kBoxStride + 32 r + 16 b, so that the buffer and the row neighbours
+// are immediate offsets of one address (the pad shifts an unknown by half the banks)
+constexpr int kBoxStride = kBoxRows * 32 + 16;
+
+struct alignas(32) BoxItem {
+    long long off;        // first cell of the first patch
+    unsigned rel[4];      // bytes from the first patch's state block to those of the 16 / p patches side by
+                          // side (unused ones: the last one's)
+    int p, ty, tz;        // patch edge, origin of the box in y and z
+    int live;             // patches to update (the others repeat the last one)
+    double inv_dx[4];
+};
+static_assert(sizeof(BoxItem) == 96, "BoxItem layout");
+// largest distance of two patches of one box in the state, so that 32-bit
+// byte offsets from the first reach every unknown of the last
+constexpr long long kBoxSpread = 1ll << 30;
+
+// RT: row tiles of 16 unknowns (16 (RT - 1) < N <= 16 RT).  FIN: the last
+// stage of RK4 (see rk_base).  out may be y1.
+template <int RT, bool FIN>
+__global__ __launch_bounds__(kBoxThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void fd_stage_box_kernel(
+    const double *__restrict__ y, const double *__restrict__ q0, const double *y1, const double *__restrict__ y2,
+    double *out, const BoxItem *__restrict__ items, int n_items, const f64x2_t *__restrict__ apk, int N, double ca,
+    double sigma, int remap)
+{
+    __shared__ double sF[4][kBoxStride];
+    constexpr int CMAX = RT < 4 ? 4 * RT : kTileMaxCh, CMIN = 4 * (RT - 1) + 1;   // chunks: CMIN <= nch <= CMAX
+    const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, lg = l >> 4, x = l & 15;
+    const int G = (int)gridDim.x, slot = remap ? xcd_remap((int)blockIdx.x, G) : (int)blockIdx.x;
+    const int n_my = (n_items - slot + G - 1) / G;   // >= 1: the grid is no larger than the list
+    const int nch = (N + 3) / 4;
+
+    // footprint loads: a chunk is 4 x 384 pieces of 16 bytes (8 per row);
+    // thread t moves pieces t + 256 i, i = 0..5, i.e. of unknown i / 3 * 2 +
+    // {0, t >= 128, 1} the row t / 8 + {0, t < 128 ? 32 : -16, 16}, piece t % 8
+    const int fx = 2 * (t & 7);
+    const bool fhi = t >= 128;
+    const char *lb = nullptr;     // unknown 0 of the first patch of the box the loads are in
+    unsigned lv[3] = {0, 0, 0};   // this thread's pieces in it (bytes); lv1: the second in its own unknown
+    unsigned lv1 = 0;
+    int lC = 0;                   // bytes per unknown
+    auto load_box = [&](int k) {
+        // (past the end: the last box again, nobody reads it)
+        const BoxItem &T = items[slot + min(k, n_my - 1) * G];
+        __asm__ volatile("");   // (stays a branch where it is in one)
+        const int p = T.p, m = p - 1;
+        const unsigned r0 = T.rel[0], r1 = T.rel[1], r2 = T.rel[2], r3 = T.rel[3];
+        unsigned r = fx >= p ? r1 : r0;
+        r = fx >= 2 * p ? r2 : r;
+        r = fx >= 3 * p ? r3 : r;
+        lb = reinterpret_cast<const char *>(y + T.off * N);
+        lC = p * p * p * 8;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int f = min((t >> 3) + (i == 0 ? 0 : i == 2 ? 16 : fhi ? -16 : 32), kBoxOwn + 23);
+            const int h = f - kBoxOwn, hz = h >> 2;
+            const int z = h < 0 ? f / 10 : hz < 3 ? hz - 3 : hz - 3 + kBoxZ, yy = h < 0 ? f % 10 - 3 : h & 3;
+            lv[i] = r + 8 * (unsigned)((((T.tz + z) & m) * p + ((T.ty + yy) & m)) * p + (fx & m));
+        }
+        lv1 = lv[1] + (fhi ? (unsigned)lC : 0u);
+    };
+    f64x2_t F[6];
+    // chunk c; `tail`: unknowns past the last one read the last one (their
+    // gradients are zeroed)
+    auto load_chunk = [&](int c, bool tail) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            const int v0 = 4 * c + i / 3 * 2, v1 = v0 + (i % 3 == 2 ? 1 : 0), v = tail ? min(v1, N - 1) : v1;
+            unsigned o = lv[i % 3];
+            if (i % 3 == 1) o = !tail || v0 + 1 < N ? lv1 : o;
+            F[i] = *reinterpret_cast<const f64x2_t *>(lb + (long long)v * lC + o);
+        }
+    };
+    const int fs = (t >> 3) * 32 + fx;   // LDS slot of piece 0
+    const int fs1 = fs + (fhi ? kBoxStride - 512 : 1024);
+    auto stage = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            double *d = &sF[i / 3 * 2][16 * b];
+            *reinterpret_cast<f64x2_t *>(d + (i % 3 == 0 ? fs : i % 3 == 1 ? fs1 : fs + kBoxStride + 512)) = F[i];
+        }
+    };
+
+    // this wave's rows of the box, and the lane's footprint slots: rows y - 3
+    // ... y + 4 of its own plane from cb (32 apart), z neighbours of the first
+    // row at zo (+ 32 for the second), x neighbours at xo
+    const int wy = 2 * (w & 1), wz = w >> 1;   // (wz < kBoxZ)
+    const int ub = lg * kBoxStride + x, cb = ub + 32 * (wz * 10 + wy);
+    int zo[6], xo[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const int z = wz + (k < 3 ? k - 3 : k - 2);
+        zo[k] = ub + 32 * ((z >= 0 && z < kBoxZ) ? z * 10 + wy + 3
+                                                 : kBoxOwn + 4 * (z < 0 ? z + 3 : z + 3 - kBoxZ) + wy);
+    }
+    auto pick = [&](int p, auto a, auto b, auto c, auto d) {
+        auto r = x >= p ? b : a;
+        r = x >= 2 * p ? c : r;
+        return x >= 3 * p ? d : r;
+    };
+
+    f64x4_t am[RT][2];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) am[rt][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    double g[3][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}}, ko[2] = {0.0, 0.0};   // of the previous step
+
+    // -sum_d B_d G_d of the previous step's chunk c.  Its A operands come in
+    // pairs (operand 2 k, 2 k + 1 of the RT row tiles of direction 0, 1, 2)
+    constexpr int AP = (3 * RT + 1) / 2;
+    f64x2_t A[AP];
+    auto load_a = [&](int c) {
+        // (from the middle, so that every piece is in reach of an immediate offset)
+        const char *ab = reinterpret_cast<const char *>(apk) + (long long)c * (AP * 1024) + 3072;
+        unsigned o = 16 * l;
+        __asm__ volatile("" : "+v"(o));
+#pragma unroll
+        for (int k = 0; k < AP; ++k) A[k] = *reinterpret_cast<const f64x2_t *>(ab + o + (1024 * k - 3072));
+    };
+    auto product = [&]() {
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const double a = A[(d * RT + rt) / 2][(d * RT + rt) % 2];
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    am[rt][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, g[d][j], am[rt][j], 0, 0, 0);
+            }
+    };
+    // stage update: the lane's cells in the box of the update
+    long long uoff = 0;
+    unsigned uv = 0;
+    int uC = 0, up = 0;
+    bool ul = false;
+    // registers i0 .. i0 + n - 1 of row tile rt of the update: unknowns
+    // 16 rt + 4 i + lg of the lane's two cells.  Loads of lanes whose unknown
+    // is beyond the last one read unknown 16 rt + 4 i (or, where that is
+    // beyond it too, unknown 0).
+    auto upd_load = [&](int rt, int i0, const double *src, auto &v) {
+        const char *b = reinterpret_cast<const char *>(src) + uoff;
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof v / sizeof v[0]); ++i) {
+            const int r = 16 * rt + 4 * (i0 + i);
+            const long long row = rt < RT - 1 || r < N ? (long long)r * uC : 0ll;
+            const unsigned o = rt < RT - 1 || r + lg < N ? uv : uv - (unsigned)(lg * uC);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) v[i][j] = *reinterpret_cast<const double *>(b + row + 8 * j * up + o);
+        }
+    };
+    auto upd_store = [&](int rt, int i0, const auto &v) {
+        char *b = reinterpret_cast<char *>(out) + uoff;
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof v / sizeof v[0]); ++i) {
+            const int r = 16 * rt + 4 * (i0 + i);
+            if (ul && (rt < RT - 1 || r + lg < N)) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    *reinterpret_cast<double *>(b + (long long)r * uC + 8 * j * up + uv) =
+                        v[i][j] + ca * am[rt][j][i0 + i];
+            }
+        }
+    };
+    auto clear = [&]() {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) am[rt][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+    };
+
+    load_box(0);
+    load_chunk(0, true);
+    stage(0);
+    if (nch == 1) load_box(1);
+    load_chunk(nch == 1 ? 0 : 1, true);
+    for (int kt = 0; kt < n_my; ++kt) {
+        const BoxItem &T = items[slot + kt * G];
+        const int p = T.p, m = p - 1;
+        const double inv_dx = pick(p, T.inv_dx[0], T.inv_dx[1], T.inv_dx[2], T.inv_dx[3]);
+        const double c4 = inv_dx / 12.0, cko = sigma * inv_dx / 64.0;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) xo[k] = cb + 96 - x + ((x & ~m) | ((x + (k < 3 ? k - 3 : k - 2)) & m));
+        uoff = T.off * N * 8;
+        uC = p * p * p * 8;
+        up = p;
+        ul = x < p * T.live;
+        uv = pick(p, T.rel[0], T.rel[1], T.rel[2], T.rel[3]) + (unsigned)(lg * uC) +
+             8 * (unsigned)(((T.tz + wz) * p + (T.ty + wy)) * p + (x & m));
+        // The older of a SIMD's two waves wins every issue slot: without
+        // priorities the first half of the work-groups finishes a quarter
+        // earlier than the second, which then runs alone (2.56 and 3.35 ms of
+        // one stage).  Work-groups i and i + G/2 share a CU; each has
+        // precedence in every other box.
+        if ((kt & 1) == (2 * (int)blockIdx.x >= G ? 1 : 0)) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+#pragma clang loop unroll(full)
+        for (int c = 0; c < CMAX; ++c) {
+            if (c >= CMIN && c >= nch) continue;   // (not break: a constant trip count lets the loop unroll)
+            lds_barrier();
+            // with an odd count of chunks the next box's first one waits for the end of this box
+            if (c < CMIN - 1 || c < nch - 1 || !(nch & 1)) {
+                stage((c + 1) & 1);
+                if (c + 2 < CMIN || c + 2 < nch) {
+                    load_chunk(c + 2, c + 2 >= CMIN - 1);
+                } else {
+                    if (c + 2 == nch) load_box(kt + 1);
+                    load_chunk(c + 2 - nch, nch < 3);
+                }
+            }
+            // 1. the stencil values of this step's unknown out of LDS
+            __builtin_amdgcn_sched_barrier(0);
+            const double *u = &sF[0][16 * (c & 1)];
+            double uy[8], ux[2][6], uz[2][6];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) uy[k] = u[cb + 32 * k];
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    ux[j][k] = u[xo[k] + 32 * j];
+                    uz[j][k] = u[zo[k] + 32 * j];
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            // 2. the previous step's matrix instructions, while the reads arrive
+            if (c > 0) product();
+            __builtin_amdgcn_sched_barrier(0);
+            // 3. this step's operands and values
+            load_a(c);
+            const bool on = c < CMIN - 1 || 4 * c + lg < N;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const double u0 = uy[3 + j];
+                double g0, g1, g2, k;
+                {
+                    const double m3 = ux[j][0], m2 = ux[j][1], m1 = ux[j][2], p1 = ux[j][3], p2 = ux[j][4],
+                                 p3 = ux[j][5];
+                    g0 = ((m2 - p2) + 8.0 * (p1 - m1)) * c4;
+                    k = ((m3 + p3) - 6.0 * (m2 + p2)) + 15.0 * (m1 + p1) - 20.0 * u0;
+                }
+                {
+                    const double m3 = uy[j], m2 = uy[j + 1], m1 = uy[j + 2], p1 = uy[j + 4], p2 = uy[j + 5],
+                                 p3 = uy[j + 6];
+                    g1 = ((m2 - p2) + 8.0 * (p1 - m1)) * c4;
+                    k += ((m3 + p3) - 6.0 * (m2 + p2)) + 15.0 * (m1 + p1) - 20.0 * u0;
+                }
+                {
+                    const double m3 = uz[j][0], m2 = uz[j][1], m1 = uz[j][2], p1 = uz[j][3], p2 = uz[j][4],
+                                 p3 = uz[j][5];
+                    g2 = ((m2 - p2) + 8.0 * (p1 - m1)) * c4;
+                    k += ((m3 + p3) - 6.0 * (m2 + p2)) + 15.0 * (m1 + p1) - 20.0 * u0;
+                }
+                g[0][j] = on ? g0 : 0.0;
+                g[1][j] = on ? g1 : 0.0;
+                g[2][j] = on ? g2 : 0.0;
+                // the previous chunk's KO6 once its product is done
+                if (c > 0) am[(c - 1) / 4][j][(c - 1) % 4] += ko[j];
+                ko[j] = on ? cko * k : 0.0;
+            }
+            // (complete before the next barrier: the compiler would rather
+            // keep the raw stencil values in registers across it)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) __asm__ volatile("" : "+v"(g[0][j]), "+v"(g[1][j]), "+v"(g[2][j]), "+v"(ko[j]));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (nch & 1) {
+            lds_barrier();
+            stage(0);
+            if (nch == 1) load_box(kt + 2);
+            load_chunk(nch == 1 ? 0 : 1, nch < 3);
+        }
+        // the last chunk, whose KO6 rows are in the last row tile, and the
+        // update.  The product hides the first loads' latency, and every load
+        // goes out before the stores it would otherwise wait behind (loads and
+        // stores complete in order).
+        auto last = [&]() {
+            product();
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) am[RT - 1][j][i] += ((nch - 1) & 3) == i ? ko[j] : 0.0;
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (!FIN) {
+            double q[RT][4][2];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) upd_load(rt, 0, q0, q[rt]);
+            __builtin_amdgcn_sched_barrier(0);
+            last();
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) upd_store(rt, 0, q[rt]);
+        } else {
+            // rounds of half a row tile (four arrays), three in flight
+            constexpr int D = 3;
+            double v[D][4][2][2];
+            auto load4 = [&](int k) {
+                upd_load(k / 2, 2 * (k & 1), q0, v[k % D][0]);
+                upd_load(k / 2, 2 * (k & 1), y1, v[k % D][1]);
+                upd_load(k / 2, 2 * (k & 1), y2, v[k % D][2]);
+                upd_load(k / 2, 2 * (k & 1), y, v[k % D][3]);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+#pragma unroll
+            for (int k = 0; k < D && k < 2 * RT; ++k) load4(k);
+            last();
+#pragma unroll
+            for (int k = 0; k < 2 * RT; ++k) {
+                double w4[2][2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        w4[i][j] = rk_base(v[k % D][0][i][j], v[k % D][1][i][j], v[k % D][2][i][j], v[k % D][3][i][j]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (k + D < 2 * RT) load4(k + D);
+                upd_store(k / 2, 2 * (k & 1), w4);
+            }
+        }
+        clear();
     }
 }
 
@@ -976,14 +1325,12 @@ pb_status fd_prepare(pb_batch *b)
             ws[i] = WsItem{off[k], p, kT * (t % nt), kT * ((t / nt) % nt), kT * (t / (nt * nt)), 1.0 / b->dx[k]};
         }
     }
-    PB_HIP(hipMalloc(&b->d_fd_ws_items, ws.size() * sizeof(WsItem)));
-    PB_HIP(hipMemcpy(b->d_fd_ws_items, ws.data(), ws.size() * sizeof(WsItem), hipMemcpyHostToDevice));
     // A operands of the one-wave-per-tile kernel: per chunk c of four
     // unknowns, direction d, row tile rt and lane l, -B_d[16 rt + l%16][4 c + l/16]
     // (zero outside N x N)
+    std::vector<double> apk((size_t)kTileMaxCh * kTileA, 0.0);
     {
         const int N = b->N;
-        std::vector<double> apk((size_t)kTileMaxCh * kTileA, 0.0);
         for (int c = 0; c < kTileMaxCh; ++c)
             for (int d = 0; d < 3; ++d)
                 for (int rt = 0; rt < 4; ++rt)
@@ -993,49 +1340,134 @@ pb_status fd_prepare(pb_batch *b)
                             apk[(size_t)c * kTileA + (d * 4 + rt) * 64 + l] =
                                 -b->params[3 + (size_t)d * N * N + (size_t)r * N + k];
                     }
-        PB_HIP(hipMalloc(&b->d_fd_A, apk.size() * sizeof(double)));
-        PB_HIP(hipMemcpy(b->d_fd_A, apk.data(), apk.size() * sizeof(double), hipMemcpyHostToDevice));
     }
-    PB_HIP(hipMalloc(&b->d_fd_items, items.size() * sizeof(FdItem)));
-    PB_HIP(hipMalloc(&b->d_fd_B, nB * sizeof(double)));
-    PB_HIP(hipMemcpy(b->d_fd_items, items.data(), items.size() * sizeof(FdItem), hipMemcpyHostToDevice));
-    PB_HIP(hipMemcpy(b->d_fd_B, b->params.data() + 3, nB * sizeof(double), hipMemcpyHostToDevice));
+    // boxes: patches of one size (largest first) in groups of 16 / p side by
+    // side (none for other sizes, which only the search can bring here)
+    std::vector<BoxItem> box;
+    if (std::all_of(b->p.begin(), b->p.end(), [](int p) { return p == 4 || p == 8 || p == 16; })) {
+        std::vector<long long> off((size_t)b->K + 1, 0);
+        for (int k = 0; k < b->K; ++k) off[k + 1] = off[k] + (long long)b->p[k] * b->p[k] * b->p[k];
+        for (size_t i = 0; i < order.size();) {
+            const int p = b->p[order[i]];
+            BoxItem T{};
+            T.p = p;
+            T.off = off[order[i]];
+            while (T.live < 16 / p && i < order.size() && b->p[order[i]] == p &&
+                   (off[order[i]] - T.off) * b->N * 8 <= kBoxSpread) {
+                for (int j = T.live; j < 4; ++j) {
+                    T.rel[j] = (unsigned)((off[order[i]] - T.off) * b->N * 8);
+                    T.inv_dx[j] = 1.0 / b->dx[order[i]];
+                }
+                ++T.live;
+                ++i;
+            }
+            for (T.tz = 0; T.tz < p; T.tz += kBoxZ)
+                for (T.ty = 0; T.ty < p; T.ty += 4) box.push_back(T);
+        }
+    }
+    // A operands of the box kernel: operand (d, rt) of chunk c and lane l is
+    // -B_d[16 rt + l%16][4 c + l/16] (zero outside N x N), the operands of a
+    // chunk in pairs of one 16-byte piece per lane
+    std::vector<double> bpk;
+    {
+        const int N = b->N, nch = (N + 3) / 4, RT = (N + 15) / 16, AP = (3 * RT + 1) / 2;
+        bpk.assign((size_t)nch * AP * 128, 0.0);
+        for (int c = 0; c < nch; ++c)
+            for (int d = 0; d < 3; ++d)
+                for (int rt = 0; rt < RT; ++rt)
+                    for (int l = 0; l < 64; ++l) {
+                        const int r = 16 * rt + l % 16, k = 4 * c + l / 16, o = d * RT + rt;
+                        if (r < N && k < N)
+                            bpk[((size_t)c * AP + o / 2) * 128 + 2 * l + o % 2] =
+                                -b->params[3 + (size_t)d * N * N + (size_t)r * N + k];
+                    }
+    }
+    // every table in one allocation, uploaded by one copy
+    struct Part {
+        const void *src;
+        size_t bytes;
+    };
+    const Part part[6] = {{items.data(), items.size() * sizeof(FdItem)}, {ws.data(), ws.size() * sizeof(WsItem)},
+                          {box.data(), box.size() * sizeof(BoxItem)},    {b->params.data() + 3, nB * sizeof(double)},
+                          {apk.data(), apk.size() * sizeof(double)},     {bpk.data(), bpk.size() * sizeof(double)}};
+    size_t at[6], total = 0;
+    for (int i = 0; i < 6; ++i) {
+        at[i] = total;
+        total += (part[i].bytes + 255) & ~(size_t)255;
+    }
+    std::vector<char> blob(total);
+    for (int i = 0; i < 6; ++i) std::memcpy(blob.data() + at[i], part[i].src, part[i].bytes);
+    void *mem = nullptr;
+    PB_HIP(hipMalloc(&mem, total));
+    const hipError_t e = hipMemcpy(mem, blob.data(), total, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(mem);
+        return hip_fail(e, "hipMemcpy(FD tables)");
+    }
+    char *m = static_cast<char *>(mem);
+    b->d_fd_mem = mem;
+    b->d_fd_items = m + at[0];
+    b->d_fd_ws_items = m + at[1];
+    b->d_fd_boxes = m + at[2];
+    b->d_fd_B = reinterpret_cast<double *>(m + at[3]);
+    b->d_fd_A = reinterpret_cast<double *>(m + at[4]);
+    b->d_fd_boxA = m + at[5];
+    b->fd_n_boxes = (int)box.size();
     b->fd_n_items = (int)items.size();
     b->fd_ready = true;
     return PB_OK;
 }
 
-pb_status launch_fd_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, void *ynext,
-                          void *acc, double dt, double sigma, hipStream_t s)
+pb_status launch_fd_stage(pb_batch *b, int stage, int rk_stages, const void *q0_, const void *y_, const void *y1_,
+                          const void *y2_, void *out_, double dt, double sigma, hipStream_t s)
 {
     pb_status st = fd_prepare(b);
     if (st != PB_OK) return st;
     if (b->N > kMaxN) { set_error("fd_ko_step: at most 60 unknowns"); return PB_EUNSUPPORTED; }
-    Ctrl *ctrl = reinterpret_cast<Ctrl *>(b->ws);
     int dev = 0, cus = 0;
     PB_HIP(hipGetDevice(&dev));
     PB_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const double *q0 = static_cast<const double *>(q0_), *y = static_cast<const double *>(y_);
+    const double *y1 = static_cast<const double *>(y1_), *y2 = static_cast<const double *>(y2_);
+    double *out = static_cast<double *>(out_);
+    const WsItem *tiles = reinterpret_cast<const WsItem *>(b->d_fd_ws_items);
+    const int fin = rk_stages == 4 && stage == 3;
+    const double ca = rk_stages == 1 || stage == 2 ? dt : fin ? dt / 6.0 : 0.5 * dt;
     if (b->fd_ws == 2) {
         // one wave per work-group, as many as the LDS holds (4 per CU)
         const int grid = std::max(1, std::min(b->fd_n_items, cus * 4));
-        launch_main(b, fd_stage_tile_kernel, dim3(grid), dim3(64), 0, s, static_cast<const double *>(y),
-                    static_cast<const double *>(q0), static_cast<double *>(ynext), static_cast<double *>(acc),
-                    reinterpret_cast<const WsItem *>(b->d_fd_ws_items), b->fd_n_items, b->d_fd_A, b->N, stage,
-                    rk_stages, dt, sigma, b->fd_xcd_remap);
-        PB_HIP(hipGetLastError());
-        return PB_OK;
-    }
-    if (b->fd_ws) {
+        launch_main(b, fd_stage_tile_kernel, dim3(grid), dim3(64), 0, s, y, q0, y1, y2, out, tiles, b->fd_n_items,
+                    b->d_fd_A, b->N, fin, ca, sigma, b->fd_xcd_remap);
+    } else if (b->fd_ws && b->fd_n_items > cus && b->fd_n_boxes > 0) {
+        // boxes, two work-groups per CU.  Up to one 4x4x4 tile per CU the
+        // wave-specialised kernel is the faster (58 unknowns, 256 tiles: 22
+        // against 27 us per stage), beyond it needs a second round (384
+        // tiles: 36 against 28 us; 4096 patches: 4.8 against 3.4 ms)
+        const int grid = std::max(1, std::min(b->fd_n_boxes, 2 * cus));
+        auto go = [&](auto kern) {
+            launch_main(b, kern, dim3(grid), dim3(kBoxThreads), 0, s, y, q0, y1, y2, out,
+                        reinterpret_cast<const BoxItem *>(b->d_fd_boxes), b->fd_n_boxes,
+                        reinterpret_cast<const f64x2_t *>(b->d_fd_boxA), b->N, ca, sigma, b->fd_xcd_remap);
+        };
+        auto rows = [&](auto rt) {
+            constexpr int RT = decltype(rt)::value;
+            if (fin) go(fd_stage_box_kernel<RT, true>);
+            else go(fd_stage_box_kernel<RT, false>);
+        };
+        switch ((b->N + 15) / 16) {
+        case 1: rows(std::integral_constant<int, 1>()); break;
+        case 2: rows(std::integral_constant<int, 2>()); break;
+        case 3: rows(std::integral_constant<int, 3>()); break;
+        default: rows(std::integral_constant<int, 4>()); break;
+        }
+    } else if (b->fd_ws) {
         // one wave-specialised work-group per CU
         const int grid = std::max(1, std::min(b->fd_n_items, cus));
-        const int nch = (b->N + kCh - 1) / kCh;
         auto go = [&](auto kern) {
-            launch_main(b, kern, dim3(grid), dim3(kWsThreads), 0, s, static_cast<const double *>(y),
-                               static_cast<const double *>(q0), static_cast<double *>(ynext),
-                               static_cast<double *>(acc), reinterpret_cast<const WsItem *>(b->d_fd_ws_items),
-                               b->fd_n_items, b->d_fd_B, b->N, stage, rk_stages, dt, sigma, b->fd_xcd_remap);
+            launch_main(b, kern, dim3(grid), dim3(kWsThreads), 0, s, y, q0, y1, y2, out, tiles, b->fd_n_items,
+                        b->d_fd_B, b->N, fin, ca, sigma, b->fd_xcd_remap);
         };
-        switch (nch) {
+        switch ((b->N + kCh - 1) / kCh) {
         case 1: go(fd_stage_ws_kernel<1>); break;
         case 2: go(fd_stage_ws_kernel<2>); break;
         case 3: go(fd_stage_ws_kernel<3>); break;
@@ -1045,14 +1477,12 @@ pb_status launch_fd_stage(pb_batch *b, int stage, int rk_stages, const void *q0,
         case 7: go(fd_stage_ws_kernel<7>); break;
         default: go(fd_stage_ws_kernel<8>); break;
         }
-        PB_HIP(hipGetLastError());
-        return PB_OK;
+    } else {
+        const int grid = std::max(1, std::min(b->fd_n_items, cus * b->fd_wg_per_cu));
+        launch_main(b, fd_stage_kernel, dim3(grid), dim3(kFdThreads), 0, s, y, q0, y1, y2, out, b->d_patches,
+                    reinterpret_cast<const FdItem *>(b->d_fd_items), b->fd_n_items, b->d_fd_B, b->N, fin, ca, sigma,
+                    b->fd_xcd_remap);
     }
-    const int grid = std::max(1, std::min(b->fd_n_items, cus * b->fd_wg_per_cu));
-    launch_main(b, fd_stage_kernel, dim3(grid), dim3(kFdThreads), 0, s, static_cast<const double *>(y),
-                       static_cast<const double *>(q0), static_cast<double *>(ynext), static_cast<double *>(acc),
-                       b->d_patches, reinterpret_cast<const FdItem *>(b->d_fd_items), b->fd_n_items,
-                       b->d_fd_B, b->N, stage, rk_stages, dt, sigma, b->fd_xcd_remap);
     PB_HIP(hipGetLastError());
     return PB_OK;
 }
