@@ -234,28 +234,12 @@ static pb_status enqueue_fd(pb_batch *b, double cfl, double dt_fixed, double sig
     pb_status st;
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
     void *yA = b->ws + L.yA, *yB = b->ws + L.yB;
-    if (b->pde == PB_PDE_EULER) {
-        // dt on the device: from Q^n for the first step, then from the last
-        // stage of each step (ping-pong slots as in the FV path)
-        if (!(dt_fixed > 0.0))
-            if ((st = launch_fv_lambda(b, b->state[cur], cfl, s)) != PB_OK) return st;
-        for (int i = 0; i < n; ++i) {
-            void *q0 = b->state[cur], *acc = b->state[cur ^ 1];
-            const int slot = i & 1;
-            void *ys[4] = {q0, yA, yB, yA};
-            void *yn[4] = {yA, yB, yA, nullptr};
-            for (int sg = 0; sg < (rk == 1 ? 1 : 4); ++sg) {
-                arm_events(b);
-                st = disarm_events(b, launch_fd_euler_stage(b, sg, rk, q0, ys[sg], rk == 1 ? nullptr : yn[sg], acc,
-                                                            slot, dt_fixed, cfl, sigma, s));
-                if (st != PB_OK) return st;
-            }
-            cur ^= 1;
-        }
-        *cur_io = cur;
-        return PB_OK;
-    }
-    const double dt = fd_dt(b, cfl, dt_fixed);
+    const bool euler = b->pde == PB_PDE_EULER;
+    // Euler: dt on the device, from Q^n for the first step, then from the last
+    // stage of each step (ping-pong slots as in the FV path)
+    if (euler && !(dt_fixed > 0.0))
+        if ((st = launch_fv_lambda(b, b->state[cur], cfl, s)) != PB_OK) return st;
+    const double dt = euler ? 0.0 : fd_dt(b, cfl, dt_fixed);
     for (int i = 0; i < n; ++i) {
         // stage 1 reads Q^n, stages 2-4 the previous stage value: y1 in the
         // other state buffer (the last stage turns it into Q^(n+1) in place),
@@ -264,8 +248,9 @@ static pb_status enqueue_fd(pb_batch *b, double cfl, double dt_fixed, double sig
         void *yin[4] = {q0, q1, yA, yB}, *yout[4] = {q1, yA, yB, q1};
         for (int sg = 0; sg < (rk == 1 ? 1 : 4); ++sg) {
             arm_events(b);
-            st = disarm_events(b, launch_fd_stage(b, sg, rk, q0, yin[sg], q1, yA, yout[sg], dt, sigma, s));
-            if (st != PB_OK) return st;
+            st = euler ? launch_fd_euler_stage(b, sg, rk, q0, yin[sg], q1, yA, yout[sg], i & 1, dt_fixed, cfl, sigma, s)
+                       : launch_fd_stage(b, sg, rk, q0, yin[sg], q1, yA, yout[sg], dt, sigma, s);
+            if ((st = disarm_events(b, st)) != PB_OK) return st;
         }
         cur ^= 1;
     }

@@ -213,6 +213,17 @@ __device__ __forceinline__ void lds_barrier()
     __asm__ volatile("s_barrier" ::: "memory");
 }
 
+// Classical RK4 with stage values y1 = Q0 + dt/2 k1, y2 = Q0 + dt/2 k2,
+// y3 = Q0 + dt k3 and no running sum of the k: the new state is
+//   Q0 + ((y1 - Q0) + 2 (y2 - Q0) + (y3 - Q0)) / 3 + dt/6 k4,
+// so stages 1-3 read Q0 and write one array each, and only the last stage
+// reads y1, y2 and its own y3: 13 passes over the state per step instead of
+// the 16 of a running sum, with two roundings of the sum instead of four.
+__device__ __forceinline__ double rk_base(double q0, double y1, double y2, double y3)
+{
+    return q0 + ((y1 - q0) + 2.0 * (y2 - q0) + (y3 - q0)) * (1.0 / 3.0);
+}
+
 __device__ __forceinline__ int xcd_remap(int bid, int n)
 {
     const int q = n >> 3, r = n & 7;
@@ -348,10 +359,12 @@ pb_status launch_srhd_c2p(pb_batch *b, const void *q, int slot_out, bool want_dt
 // values y1 and y2, and out may be y1
 pb_status launch_fd_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, const void *y1,
                           const void *y2, void *out, double dt, double sigma, hipStream_t s);
-// one stage of the Euler FD4 + KO6 step (dt from ctrl->dt[slot] unless
-// dt_fixed > 0; the last stage writes the next step's dt to slot ^ 1)
-pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, void *ynext,
-                                void *acc, int slot, double dt_fixed, double cfl, double sigma, hipStream_t s);
+// one stage of the Euler FD4 + KO6 step, with the buffers of launch_fd_stage
+// (dt from ctrl->dt[slot] unless dt_fixed > 0; the last stage writes the next
+// step's dt to slot ^ 1)
+pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, const void *y1,
+                                const void *y2, void *out, int slot, double dt_fixed, double cfl, double sigma,
+                                hipStream_t s);
 // the DMA-fed FV kernel applies to this batch (3D, no extra per-cell input,
 // every p a multiple of 4, 16-byte aligned state buffers)
 bool fv_dma_eligible(const pb_batch *b);

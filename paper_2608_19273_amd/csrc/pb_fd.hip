@@ -164,17 +164,6 @@ __device__ __forceinline__ void barrier_keep(int pending)
     __asm__ volatile("s_barrier" ::: "memory");
 }
 
-// Classical RK4 with stage values y1 = Q0 + dt/2 k1, y2 = Q0 + dt/2 k2,
-// y3 = Q0 + dt k3 and no running sum of the k: the new state is
-//   Q0 + ((y1 - Q0) + 2 (y2 - Q0) + (y3 - Q0)) / 3 + dt/6 k4,
-// so stages 1-3 read Q0 and write one array each, and only the last stage
-// reads y1, y2 and its own y3: 13 passes over the state per step instead of
-// the 16 of a running sum, with two roundings of the sum instead of four.
-__device__ __forceinline__ double rk_base(double q0, double y1, double y2, double y3)
-{
-    return q0 + ((y1 - q0) + 2.0 * (y2 - q0) + (y3 - q0)) * (1.0 / 3.0);
-}
-
 // LDS writes done, then the work-group barrier
 __device__ __forceinline__ void barrier_lds()
 {

@@ -119,27 +119,35 @@ __device__ __forceinline__ void load5u_nt(const double *__restrict__ base, unsig
 
 }  // namespace
 
-// S: RK4 stage 0..3, or 4 for the single forward-Euler stage.
-//   S = 0: ynext = y + dt/2 R, acc = y + dt/6 R      (y = Q^n)
-//   S = 1: ynext = q0 + dt/2 R, acc += dt/3 R
-//   S = 2: ynext = q0 + dt R,   acc += dt/3 R
-//   S = 3: acc += dt/6 R                              (acc = Q^{n+1})
-//   S = 4: acc = y + dt R                             (y = Q^n)
-// kLam: fold the speeds of the new state (last stage, CFL mode).
+// S: RK4 stage 0..3, or 4 for the single forward-Euler stage (rk_base has the
+// scheme; y is the stage input, out may be y1).
+//   S = 0: out = y + dt/2 R          (y = Q^n)
+//   S = 1: out = q0 + dt/2 R
+//   S = 2: out = q0 + dt R
+//   S = 3: out = rk_base(q0, y1, y2, y) + dt/6 R
+//   S = 4: out = y + dt R            (y = Q^n)
+// Bound: issue at 2 waves per SIMD in stages 0-2 (256 to 277 us on 2048 16^3
+// patches; they move 2 and 3 arrays of 336 MB, 106 and 160 us at the copy
+// rate), memory in stage 3 (350 us for 5 arrays and the halo strips).  With a
+// running sum of the k the stages moved 3, 5, 5 and 3 arrays in 291, 342, 346
+// and 298 us.
+// The final stages (3 and 4) fold the speeds of the new state into partials,
+// with a fixed dt too, where nobody reads them: without that code the compiler
+// orders the stage so that it spills 37 registers (two steps of 2048 16^3
+// patches with a fixed dt: 2102 us without it, 1927 us with it).
 // runs (non-null): unit u marches runs[u] = (patch, first plane, planes, 0)
 // up the patch's +z chain, crossing patch tops without a restart (the
 // column-run table of the FV kernel); else unit u is slab u % n_slabs of
 // patch u / n_slabs.
-template <int S, bool kLam>
+template <int S>
 __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
-    const double *__restrict__ y, const double *__restrict__ q0, double *__restrict__ ynext,
-    double *__restrict__ acc, const PatchDev *__restrict__ patches, int n_units, int n_slabs, int slab, int remap,
+    const double *__restrict__ y, const double *__restrict__ q0, const double *y1, const double *__restrict__ y2,
+    double *out, const PatchDev *__restrict__ patches, int n_units, int n_slabs, int slab, int remap,
     const int4 *__restrict__ runs, Ctrl *__restrict__ ctrl, double *__restrict__ part, int slot, double dt_fixed,
     double gamma, double sigma)
 {
     constexpr int N = kEN;
-    constexpr bool kReadQ0 = S == 1 || S == 2;
-    constexpr bool kReadAcc = S == 1 || S == 2 || S == 3;
+    constexpr bool kReadQ0 = S == 1 || S == 2 || S == 3;
     constexpr bool kFinal = S == 3 || S == 4;
     __shared__ double sQ[N][kPlaneQ];
     __shared__ double sFx[N][kPlaneF];
@@ -167,8 +175,8 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
     const double *yo = y + patches[kc].off * N, *ylo = y + patches[patches[kc].nbr[4]].off * N;
     int kn = patches[kc].nbr[5];
     const double *yhi = y + patches[kn].off * N;
-    const double *q0o = q0 + patches[kc].off * N, *acco = acc + patches[kc].off * N;
-    double *yno = ynext + patches[kc].off * N, *accw = acc + patches[kc].off * N;
+    const double *q0o = q0 + patches[kc].off * N, *y1o = y1 + patches[kc].off * N, *y2o = y2 + patches[kc].off * N;
+    double *outo = out + patches[kc].off * N;
     double inv_dx = patches[kc].inv_dx;
     // a slab can start beyond the last plane of a patch smaller than the
     // batch maximum: such a unit only takes part in the reductions
@@ -177,6 +185,7 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
     const int x = active ? t % p : 0, yy = active ? t / p : 0;
     const unsigned cxy = (unsigned)(yy * p + x), cxy8 = 8u * cxy;
     const double dt = dt_fixed > 0.0 ? dt_fixed : ctrl->dt[slot];
+    const double ca = S == 2 || S == 4 ? dt : S == 3 ? dt / 6.0 : 0.5 * dt;
     const double gm1 = gamma - 1.0;
     double c4 = inv_dx / 12.0, cko = sigma * inv_dx / 64.0;
     const Euler<3> ph{gamma};
@@ -267,7 +276,7 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
         auto A = [&](int w) -> double * { return ar[(w + PH) % 7]; };
         const size_t zo = (size_t)z * pp;   // the plane's first cell in the patch block
         const unsigned ob = cxy8;
-        double q0v[N], accv[N];
+        double q0v[N], y1v[N], y2v[N];
         {
             // plane z+3 enters the window; the load of plane z+4 replaces it
             // (near the run's top a plane inside the window's reach is
@@ -277,7 +286,10 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
             for (int v = 0; v < N; ++v) Q(6)[v] = rl[v];
             col(z + min(4, n + 2 - i), ob, rl);
             if (kReadQ0) load5u_nt(q0o + zo, ob, C, q0v);
-            if (kReadAcc) load5u_nt(acco + zo, ob, C, accv);
+            if (S == 3) {
+                load5u_nt(y1o + zo, ob, C, y1v);
+                load5u_nt(y2o + zo, ob, C, y2v);
+            }
             euler_ip(Q(5), gm1, A(5));
         }
         if (active) {
@@ -369,33 +381,19 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
             double nv[N];
 #pragma unroll
             for (int v = 0; v < N; ++v) {
-                double *const yg = at(yno + zo + (size_t)v * C, ob), *const ag = at(accw + zo + (size_t)v * C, ob);
-                if (S == 0) {
-                    __builtin_nontemporal_store(Q(3)[v] + (0.5 * dt) * R[v], yg);
-                    nv[v] = Q(3)[v] + (dt / 6.0) * R[v];
-                } else if (S == 1) {
-                    __builtin_nontemporal_store(q0v[v] + (0.5 * dt) * R[v], yg);
-                    nv[v] = accv[v] + (dt / 3.0) * R[v];
-                } else if (S == 2) {
-                    __builtin_nontemporal_store(q0v[v] + dt * R[v], yg);
-                    nv[v] = accv[v] + (dt / 3.0) * R[v];
-                } else if (S == 3) {
-                    nv[v] = accv[v] + (dt / 6.0) * R[v];
-                } else {
-                    nv[v] = Q(3)[v] + dt * R[v];
-                }
-                __builtin_nontemporal_store(nv[v], ag);
+                const double c = Q(3)[v];
+                const double base = S == 0 || S == 4 ? c : S == 3 ? rk_base(q0v[v], y1v[v], y2v[v], c) : q0v[v];
+                nv[v] = base + ca * R[v];
+                __builtin_nontemporal_store(nv[v], at(outo + zo + (size_t)v * C, ob));
             }
             if (kFinal) {
 #pragma unroll
                 for (int v = 0; v < N; ++v) bad |= !isfinite(nv[v]);
-                if (kLam) {
-                    double a[3];
-                    ph.aux_fast(nv, nullptr, a);
-                    lm[0] = fmax(lm[0], ph.eig<0>(nv, a));
-                    lm[1] = fmax(lm[1], ph.eig<1>(nv, a));
-                    lm[2] = fmax(lm[2], ph.eig<2>(nv, a));
-                }
+                double a[3];
+                ph.aux_fast(nv, nullptr, a);
+                lm[0] = fmax(lm[0], ph.eig<0>(nv, a));
+                lm[1] = fmax(lm[1], ph.eig<1>(nv, a));
+                lm[2] = fmax(lm[2], ph.eig<2>(nv, a));
             }
         }
         if (++z == p && i + 1 < n) {
@@ -407,9 +405,9 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
             ylo = yo;
             yo = yhi;
             q0o = q0 + off * N;
-            acco = acc + off * N;
-            yno = ynext + off * N;
-            accw = acc + off * N;
+            y1o = y1 + off * N;
+            y2o = y2 + off * N;
+            outo = out + off * N;
             inv_dx = patches[kn].inv_dx;
             c4 = inv_dx / 12.0;
             cko = sigma * inv_dx / 64.0;
@@ -438,7 +436,7 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
     }
     if (kFinal) {
         if (__syncthreads_or(bad) && t == 0) atomicAdd(&ctrl->nonfinite, 1ull);
-        if (kLam) store_partial<3>(part, lm, unit, n_units);
+        store_partial<3>(part, lm, unit, n_units);
     }
 }
 
@@ -475,15 +473,14 @@ constexpr int kSmallW = 7;   // Q (5), 1/rho, p per slot
 
 }  // namespace
 
-template <int S, bool kLam>
+template <int S>
 __global__ __launch_bounds__(kFvThreads) void fd_euler_small_kernel(
-    const double *__restrict__ y, const double *__restrict__ q0, double *__restrict__ ynext,
-    double *__restrict__ acc, const PatchDev *__restrict__ patches, int K, int p, int G, Ctrl *__restrict__ ctrl,
+    const double *__restrict__ y, const double *__restrict__ q0, const double *y1, const double *__restrict__ y2,
+    double *out, const PatchDev *__restrict__ patches, int K, int p, int G, Ctrl *__restrict__ ctrl,
     double *__restrict__ part, int slot, double dt_fixed, double gamma, double sigma)
 {
     constexpr int N = kEN;
-    constexpr bool kReadQ0 = S == 1 || S == 2;
-    constexpr bool kReadAcc = S == 1 || S == 2 || S == 3;
+    constexpr bool kReadQ0 = S == 1 || S == 2 || S == 3;
     constexpr bool kFinal = S == 3 || S == 4;
     extern __shared__ double sm[];   // [kSmallW][G * slots]
     const SmallGeom geo{p, p * p, p * p * p, p * p * p + 18 * p * p};
@@ -494,6 +491,7 @@ __global__ __launch_bounds__(kFvThreads) void fd_euler_small_kernel(
     const bool active = g < G && k0 + g < K;
     const int x = l % p, yy = (l / p) % p, z = l / geo.p2;
     const double dt = dt_fixed > 0.0 ? dt_fixed : ctrl->dt[slot];
+    const double ca = S == 2 || S == 4 ? dt : S == 3 ? dt / 6.0 : 0.5 * dt;
     const double gm1 = gamma - 1.0;
     const Euler<3> ph{gamma};
     const unsigned C = (unsigned)geo.p3;
@@ -585,45 +583,33 @@ __global__ __launch_bounds__(kFvThreads) void fd_euler_small_kernel(
         dir(std::integral_constant<int, 1>());
         dir(std::integral_constant<int, 2>());
         const unsigned own = (unsigned)l;
-        double q0v[N], accv[N], nv[N];
+        double q0v[N], y1v[N], y2v[N], nv[N];
         if (kReadQ0) load5(q0 + off * N, own, C, q0v);
-        if (kReadAcc) load5(acc + off * N, own, C, accv);
-        double *yno = ynext + off * N, *accw = acc + off * N;
+        if (S == 3) {
+            load5(y1 + off * N, own, C, y1v);
+            load5(y2 + off * N, own, C, y2v);
+        }
+        double *outo = out + off * N;
 #pragma unroll
         for (int v = 0; v < N; ++v) {
             const double Rv = cko * kox[v] - c4 * R[v];
-            const unsigned gi = own + v * C;
-            if (S == 0) {
-                yno[gi] = qc[v] + (0.5 * dt) * Rv;
-                nv[v] = qc[v] + (dt / 6.0) * Rv;
-            } else if (S == 1) {
-                yno[gi] = q0v[v] + (0.5 * dt) * Rv;
-                nv[v] = accv[v] + (dt / 3.0) * Rv;
-            } else if (S == 2) {
-                yno[gi] = q0v[v] + dt * Rv;
-                nv[v] = accv[v] + (dt / 3.0) * Rv;
-            } else if (S == 3) {
-                nv[v] = accv[v] + (dt / 6.0) * Rv;
-            } else {
-                nv[v] = qc[v] + dt * Rv;
-            }
-            accw[gi] = nv[v];
+            const double base = S == 0 || S == 4 ? qc[v] : S == 3 ? rk_base(q0v[v], y1v[v], y2v[v], qc[v]) : q0v[v];
+            nv[v] = base + ca * Rv;
+            outo[own + v * C] = nv[v];
         }
         if (kFinal) {
 #pragma unroll
             for (int v = 0; v < N; ++v) bad |= !isfinite(nv[v]);
-            if (kLam) {
-                double a[3];
-                ph.aux_fast(nv, nullptr, a);
-                lm[0] = fmax(lm[0], ph.eig<0>(nv, a));
-                lm[1] = fmax(lm[1], ph.eig<1>(nv, a));
-                lm[2] = fmax(lm[2], ph.eig<2>(nv, a));
-            }
+            double a[3];
+            ph.aux_fast(nv, nullptr, a);
+            lm[0] = fmax(lm[0], ph.eig<0>(nv, a));
+            lm[1] = fmax(lm[1], ph.eig<1>(nv, a));
+            lm[2] = fmax(lm[2], ph.eig<2>(nv, a));
         }
     }
     if (kFinal) {
         if (__syncthreads_or(bad) && t == 0) atomicAdd(&ctrl->nonfinite, 1ull);
-        if (kLam) store_partial<3>(part, lm, blockIdx.x, gridDim.x);
+        store_partial<3>(part, lm, blockIdx.x, gridDim.x);
     }
 }
 
@@ -632,18 +618,18 @@ __global__ __launch_bounds__(kFvThreads) void fd_euler_small_kernel(
 namespace {
 
 // G > 0: the small-patch kernel with G patches per work-group (n_units = work-groups)
-template <int S, bool kLam>
-void launch_s(dim3 g, hipStream_t s, const double *y, const double *q0, double *yn, double *acc, const pb_batch *b,
-              int n_units, int n_slabs, int slab, const int4 *runs, int G, Ctrl *ctrl, double *part, int slot,
+template <int S>
+void launch_s(dim3 g, hipStream_t s, const double *y, const double *q0, const double *y1, const double *y2, double *out,
+              const pb_batch *b, int n_units, int n_slabs, int slab, const int4 *runs, int G, Ctrl *ctrl, double *part, int slot,
               double dt_fixed, double sigma)
 {
     if (G > 0) {
         const int p = b->p[0];
         const size_t lds = (size_t)kSmallW * G * (p * p * p + 18 * p * p) * sizeof(double);
-        launch_main(b, fd_euler_small_kernel<S, kLam>, g, dim3(kFvThreads), lds, s, y, q0, yn, acc,
+        launch_main(b, fd_euler_small_kernel<S>, g, dim3(kFvThreads), lds, s, y, q0, y1, y2, out,
                            b->d_patches, b->K, p, G, ctrl, part, slot, dt_fixed, b->params[0], sigma);
     } else {
-        launch_main(b, fd_euler_stage_kernel<S, kLam>, g, dim3(kFvThreads), 0, s, y, q0, yn, acc, b->d_patches,
+        launch_main(b, fd_euler_stage_kernel<S>, g, dim3(kFvThreads), 0, s, y, q0, y1, y2, out, b->d_patches,
                            n_units, n_slabs, slab, b->fd_xcd_remap, runs, ctrl, part, slot, dt_fixed, b->params[0],
                            sigma);
     }
@@ -651,8 +637,9 @@ void launch_s(dim3 g, hipStream_t s, const double *y, const double *q0, double *
 
 }  // namespace
 
-pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, void *ynext,
-                                void *acc, int slot, double dt_fixed, double cfl, double sigma, hipStream_t s)
+pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, const void *y1,
+                                const void *y2, void *out, int slot, double dt_fixed, double cfl, double sigma,
+                                hipStream_t s)
 {
     if (b->pmax > kFvPmax) { set_error("fd_ko_step: p > 16 is not supported for EULER"); return PB_EUNSUPPORTED; }
     const int slab = b->pmax, n_slabs = 1;
@@ -672,18 +659,18 @@ pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const voi
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
     double *part = reinterpret_cast<double *>(b->ws + L.part);
     const int S = rk_stages == 1 ? 4 : stage;
-    const bool final_stage = S == 3 || S == 4;
-    const bool lam = final_stage && !(dt_fixed > 0.0);
+    const bool lam = (S == 3 || S == 4) && !(dt_fixed > 0.0);
     const double *yi = static_cast<const double *>(y), *q0i = static_cast<const double *>(q0);
-    double *yn = static_cast<double *>(ynext), *ac = static_cast<double *>(acc);
+    const double *y1i = static_cast<const double *>(y1), *y2i = static_cast<const double *>(y2);
+    double *o = static_cast<double *>(out);
     const dim3 g(n_units);
-#define PB_FDE_ARGS g, s, yi, q0i, yn, ac, b, n_units, n_slabs, slab, runs, G, ctrl, part, slot, dt_fixed, sigma
+#define PB_FDE_ARGS g, s, yi, q0i, y1i, y2i, o, b, n_units, n_slabs, slab, runs, G, ctrl, part, slot, dt_fixed, sigma
     switch (S) {
-    case 0: launch_s<0, false>(PB_FDE_ARGS); break;
-    case 1: launch_s<1, false>(PB_FDE_ARGS); break;
-    case 2: launch_s<2, false>(PB_FDE_ARGS); break;
-    case 3: lam ? launch_s<3, true>(PB_FDE_ARGS) : launch_s<3, false>(PB_FDE_ARGS); break;
-    default: lam ? launch_s<4, true>(PB_FDE_ARGS) : launch_s<4, false>(PB_FDE_ARGS); break;
+    case 0: launch_s<0>(PB_FDE_ARGS); break;
+    case 1: launch_s<1>(PB_FDE_ARGS); break;
+    case 2: launch_s<2>(PB_FDE_ARGS); break;
+    case 3: launch_s<3>(PB_FDE_ARGS); break;
+    default: launch_s<4>(PB_FDE_ARGS); break;
     }
 #undef PB_FDE_ARGS
     PB_HIP(hipGetLastError());
