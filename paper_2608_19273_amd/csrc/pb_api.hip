@@ -42,7 +42,13 @@ WsLayout ws_layout(int pde, int dim, int h, long long total_cells, int N, int st
     o = align256(o);
     L.part = o;
     // [8][units] partials, then [8][units / 256 + 1] for the second reduction stage
-    o = align256(o + (size_t)8 * ((size_t)max_units(K) + (size_t)max_units(K) / 256 + 1) * sizeof(double));
+    const size_t part = (size_t)8 * ((size_t)max_units(K) + (size_t)max_units(K) / 256 + 1) * sizeof(double);
+    // the hand-over lines take the end of the partials, beyond the 3 K values
+    // that the first kernel of an FV call stores (K = 1: 136 values, 96 of
+    // them in lines; K = 4: 520 and 384)
+    L.n_lines = K >= 4 ? kLines : 2;
+    L.lines = (o + part - (size_t)3 * L.n_lines * 128) / 128 * 128;
+    o = align256(o + part);
     if (pde == PB_PDE_SRHD) {
         L.pres = o;
         o = align256(o + (size_t)total_cells * sizeof(double));
@@ -197,7 +203,7 @@ static pb_status enqueue_fv(pb_batch *b, double cfl, double dt_fixed, int n, hip
     pb_status st;
     const bool cfl_mode = !(dt_fixed > 0.0);
     if (cfl_mode && b->pde != PB_PDE_SRHD)
-        if ((st = launch_fv_lambda(b, b->state[cur], cfl, s)) != PB_OK) return st;
+        if ((st = launch_fv_lambda(b, b->state[cur], cfl, false, s)) != PB_OK) return st;
     // span mode: without the con2prim pass the n step launches follow each
     // other with nothing in between, so one pair brackets all of them
     const bool span = b->prof_span && b->pde != PB_PDE_SRHD;
@@ -238,7 +244,7 @@ static pb_status enqueue_fd(pb_batch *b, double cfl, double dt_fixed, double sig
     // Euler: dt on the device, from Q^n for the first step, then from the last
     // stage of each step (ping-pong slots as in the FV path)
     if (euler && !(dt_fixed > 0.0))
-        if ((st = launch_fv_lambda(b, b->state[cur], cfl, s)) != PB_OK) return st;
+        if ((st = launch_fv_lambda(b, b->state[cur], cfl, true, s)) != PB_OK) return st;
     const double dt = euler ? 0.0 : fd_dt(b, cfl, dt_fixed);
     for (int i = 0; i < n; ++i) {
         // stage 1 reads Q^n, stages 2-4 the previous stage value: y1 in the

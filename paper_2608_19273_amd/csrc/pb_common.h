@@ -42,8 +42,7 @@ struct Ctrl {
     unsigned int c2p_maxit;
     unsigned int pad0;
     double last_dt;
-    unsigned long long lmax[3][3];      // FV steps of a call: largest speeds (IEEE bits) by step % 3
-    unsigned long long pad[10];
+    unsigned long long pad[19];
 };
 static_assert(sizeof(Ctrl) == 256, "Ctrl layout");
 
@@ -77,9 +76,41 @@ __device__ __forceinline__ double wave_max(double v)
     return v;
 }
 
-__device__ __forceinline__ unsigned long long dbits(double v)
+// the value of the lane that a DPP control selects
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v)
 {
-    return (unsigned long long)__double_as_longlong(v);
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// the same in the rows of ROWS; the other rows keep their own value
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_rows(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// largest value of each eight lanes, in all of them (no LDS traffic)
+__device__ __forceinline__ double max8(double v)
+{
+    v = fmax(v, dpp<0x141>(v));   // mirrored in the eight
+    v = fmax(v, dpp<0x1b>(v));    // mirrored in the four
+    return fmax(v, dpp<0xb1>(v)); // neighbours swapped
+}
+
+// largest value of a wave, in its last lane
+__device__ __forceinline__ double wave_max_last(double v)
+{
+    v = max8(v);
+    v = fmax(v, dpp<0x140>(v));                  // mirrored in the row of 16
+    v = fmax(v, dpp_rows<0x142, 0xa>(v));        // last lane of rows 0, 2 to rows 1, 3
+    return fmax(v, dpp_rows<0x143, 0xc>(v));     // last lane of row 1 to rows 2, 3
 }
 
 // Work-group order -> unit order such that the units one XCD runs (the
@@ -133,71 +164,75 @@ __device__ __forceinline__ void store_partial(double *__restrict__ part, const d
 }
 
 // Hand-over of the CFL maxima between the FV steps of one call, with no
-// reduction kernel between them.  Step i of a call (step >= 0) folds the
-// largest speeds of its new state into lmax[i % 3] by atomicMax on the
-// IEEE-754 bit patterns: exact and independent of the order, since the
-// maxima are >= 0 and never NaN (fmax from 0 drops NaN speeds) and such
-// doubles order as their bit patterns.  Step i > 0 takes dt from
-// lmax[(i - 1) % 3] with the reduction kernel's arithmetic
-// (dt = cfl / sum_d Lambda_d / dx_min); its work-group 0 records that dt in
-// ctrl->dt[slot] for the host and clears lmax[(i + 1) % 3] for step i + 1
-// (last written two steps before and last read one step before, by kernels
-// that have finished).  Step 0 reads ctrl->dt[slot], which the reduction at
-// the start of the call writes; that reduction also clears lmax[0].
-// step < 0: the step stores its partials for a reduction kernel instead.
+// reduction kernel.  The call's first kernel stores the largest speeds of the
+// starting state as at most kLamUnits partials [DIM][n_part]; step 0 reduces
+// them in every work-group.  Step i folds the largest speeds of its new state
+// into slot i % 3 by atomicMax on the IEEE-754 bit patterns: exact and
+// independent of the order, since the maxima are >= 0 and never NaN (fmax
+// from 0 drops NaN speeds) and such doubles order as their bit patterns.  Step
+// i > 0 takes dt from slot (i - 1) % 3.  Both form dt = cfl / sum_d Lambda_d /
+// dx_min as the reduction kernel does, and work-group 0 records it in
+// ctrl->dt[slot] for the host.  Slot 0 is cleared by the call's first kernel
+// and slot (i + 1) % 3 by work-group 0 of step i: last written two steps
+// before and last read one step before, by kernels that have finished.
+// A slot has up to kLines cache lines of its own and a work-group folds into
+// one of them.  One line for everything took about 1.6 ns per atomic (42 us
+// of a 116 us step of 8694 work-groups); eight lines that hold all three
+// slots were no better where the work-groups read one slot while others fold
+// into the next (132 us): a slot's lines are read or folded into, not both.
+constexpr int kLamUnits = 1024;
+constexpr int kLines = 8;
 struct FvChain {
     int step;
     double cfl, dxmin;
+    unsigned long long *lines;   // [3 slots][n_lines][16], direction d at d
+    int n_lines;                 // a power of two, at most kLines
+    const double *part;          // step 0: the partials
+    int n_part;
 };
 
 template <int DIM>
-__device__ __forceinline__ double chain_dt(const Ctrl *ctrl, const FvChain &c)
+__device__ __forceinline__ double chain_dt(const double *lam, const FvChain &c)
 {
-    const int r = (c.step + 2) % 3;
     double den = 0.0;
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) den += __longlong_as_double((long long)ctrl->lmax[r][d]) / c.dxmin;
+    for (int d = 0; d < DIM; ++d) den += lam[d] / c.dxmin;
     return c.cfl / den;
 }
 
-// the step's dt: fixed, handed over from the previous step of the call, or
-// from the reduction kernel (see FvChain)
+// the step's dt: fixed, from the call's starting state, handed over from the
+// previous step of the call, or from the reduction kernel (SRHD).  Every
+// thread of the work-group calls it.
 template <int DIM, bool kLam>
-__device__ __forceinline__ double step_dt(Ctrl *ctrl, int slot_in, double dt_fixed, const FvChain &c)
+__device__ __forceinline__ double step_dt(const Ctrl *ctrl, int slot_in, double dt_fixed, const FvChain &c)
 {
-    if (dt_fixed > 0.0) return dt_fixed;
-    if (kLam && c.step > 0) {
-        const double dt = chain_dt<DIM>(ctrl, c);
-        if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->dt[slot_in] = dt;
-        return dt;
-    }
-    return ctrl->dt[slot_in];
-}
-
-// the largest speeds of a work-group's cells: to the partials (c.step < 0)
-// or folded into the control block (see FvChain)
-template <int DIM>
-__device__ __forceinline__ void fold_speeds(Ctrl *ctrl, double *__restrict__ part, const double *lm, int unit,
-                                            int n_units, const FvChain &c)
-{
-    if (c.step < 0) {
-        store_partial<DIM>(part, lm, unit, n_units);
-        return;
-    }
-    __shared__ double red[3][kFvThreads / kWave];
-    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    if (!kLam) return dt_fixed > 0.0 ? dt_fixed : ctrl->dt[slot_in];
+    const int t = threadIdx.x, lane = t & (kWave - 1);
+    double lam[DIM];
 #pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-        const double m = wave_max(lm[d]);
-        if (lane == 0) red[d][w] = m;
+    for (int d = 0; d < DIM; ++d) lam[d] = 0.0;
+    if (c.step == 0) {
+        __shared__ double red[DIM][kFvThreads / kWave];
+        for (int i = t; i < c.n_part; i += kFvThreads)
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) lam[d] = fmax(lam[d], c.part[d * c.n_part + i]);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+            lam[d] = wave_max(lam[d]);
+            if (lane == 0) red[d][t / kWave] = lam[d];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < DIM; ++d)
+#pragma unroll
+            for (int w = 0; w < kFvThreads / kWave; ++w) lam[d] = fmax(lam[d], red[d][w]);
+    } else {
+        static_assert(kLines == 8, "one line per lane of eight");
+        const unsigned long long *l = c.lines + 16 * ((c.step + 2) % 3 * c.n_lines + (lane & (c.n_lines - 1)));
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) lam[d] = max8(__longlong_as_double((long long)l[d]));
     }
-    __syncthreads();
-    if (t < DIM) {
-        double m = red[t][0];
-        for (int i = 1; i < (int)(blockDim.x / kWave); ++i) m = fmax(m, red[t][i]);
-        atomicMax(&ctrl->lmax[c.step % 3][t], (unsigned long long)__double_as_longlong(m));
-    }
-    if (blockIdx.x == 0 && t >= kWave && t < kWave + 3) ctrl->lmax[(c.step + 1) % 3][t - kWave] = 0ull;
+    return chain_dt<DIM>(lam, c);
 }
 
 // Work-group barrier for the LDS exchange only: wait for this wave's LDS
@@ -222,6 +257,47 @@ __device__ __forceinline__ void lds_barrier()
 __device__ __forceinline__ double rk_base(double q0, double y1, double y2, double y3)
 {
     return q0 + ((y1 - q0) + 2.0 * (y2 - q0) + (y3 - q0)) * (1.0 / 3.0);
+}
+
+// End of a step's work-group: counts it in ctrl->nonfinite if a lane saw a
+// NaN or infinity, folds its cells' largest speeds into the hand-over and
+// records the step's dt for the host (see FvChain).  The exchange between the
+// lanes runs on DPP moves and the one barrier waits for LDS only, so that the
+// work-group's last stores drain after it has ended its own work.
+template <int DIM, bool kLam>
+__device__ __forceinline__ void finish_step(Ctrl *ctrl, int slot_in, double dt, const double *lm, bool bad,
+                                            const FvChain &c)
+{
+    constexpr int W = kFvThreads / kWave;
+    __shared__ double red[DIM][W];
+    __shared__ int sbad[W];
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    const bool any = __ballot(bad) != 0;
+    if (lane == 0) sbad[w] = any;
+    if (kLam) {
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) {
+            const double m = wave_max_last(lm[d]);
+            if (lane == kWave - 1) red[d][w] = m;
+        }
+    }
+    lds_barrier();
+    if (t == 0) {
+        int b = 0;
+        for (int i = 0; i < W; ++i) b |= sbad[i];
+        if (b) atomicAdd(&ctrl->nonfinite, 1ull);
+        if (kLam && blockIdx.x == 0) ctrl->dt[slot_in] = dt;
+    }
+    if (kLam && t < DIM) {
+        double m = red[t][0];
+        for (int i = 1; i < W; ++i) m = fmax(m, red[t][i]);
+        atomicMax(c.lines + 16 * (c.step % 3 * c.n_lines + (blockIdx.x & (c.n_lines - 1))) + t,
+                  (unsigned long long)__double_as_longlong(m));
+    }
+    if (kLam && blockIdx.x == 0 && t >= kWave && t < kWave + c.n_lines) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) c.lines[16 * ((c.step + 1) % 3 * c.n_lines + t - kWave) + d] = 0ull;
+    }
 }
 
 __device__ __forceinline__ int xcd_remap(int bid, int n)
@@ -314,6 +390,8 @@ namespace pb {
 struct WsLayout {
     size_t ctrl = 0;       // Ctrl
     size_t part = 0;       // per-unit partials [8][units]: speeds (3), con2prim stats (5)
+    size_t lines = 0;      // FV hand-over lines (FvChain), in the tail of the partials: no step uses both
+    int n_lines = 0;
     size_t pres = 0;       // SRHD: pressure per cell (double)
     size_t yA = 0, yB = 0; // FD: stage buffers
     size_t total = 0;
@@ -349,7 +427,9 @@ inline void launch_main(const pb_batch *b, void (*kern)(P...), dim3 grid, dim3 b
 }
 
 // launchers (implemented in the kernel translation units)
-pb_status launch_fv_lambda(pb_batch *b, const void *q, double cfl, hipStream_t s);
+// largest speeds of state q: partials for the first step of an FV call, or
+// (reduce) reduced to dt in ctrl->dt[0]
+pb_status launch_fv_lambda(pb_batch *b, const void *q, double cfl, bool reduce, hipStream_t s);
 pb_status launch_fv_step(pb_batch *b, const void *qin, void *qout, int slot_in, int step, double dt_fixed,
                          double cfl, hipStream_t s);
 pb_status launch_srhd_c2p(pb_batch *b, const void *q, int slot_out, bool want_dt, double cfl,

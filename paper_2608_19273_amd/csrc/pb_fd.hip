@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kFdThreads, 2) void fd_stage_kernel(
 //     (s+1) % 2); footprint of chunk s + 2 into LDS from registers, then the
 //     global loads of chunk s + 4 into those registers; the stage results
 //     held in the ring slot of chunk s + 1 (those of chunk s + 1 - R) out to
-//     HBM, then the stage-update operands (Q^0 and accumulator rows) of
+//     HBM, then the stage-update operands (the base value of each cell) of
 //     chunk s + 1 into that slot from registers, then the loads of chunk
 //     s + 3;
 //   consumers, step s: matrix-core product of chunk s (slot s % 2) and, at

@@ -16,9 +16,8 @@
 //      the new state into a per-thread maximum.
 // LDS is double-buffered by plane parity, so one barrier per plane suffices.
 // At the end the work-group reduces its maxima (wave shuffle, then LDS) and
-// does one atomicMax per direction on the IEEE bits (exact and
-// order-independent for non-negative doubles); the last work-group to finish
-// turns the maxima into the next step's dt, so dt never leaves the device.
+// folds them into the hand-over to the call's next step (FvChain), so dt never
+// leaves the device.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -141,8 +140,7 @@ struct FvPlan {
 template <class Ph, int DIM, typename T, bool kLam>
 __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3))) void fv_step_kernel(
     const T *__restrict__ qin, T *__restrict__ qout, const double *__restrict__ ex,
-    const PatchDev *__restrict__ patches, FvPlan plan, Ctrl *__restrict__ ctrl, double *__restrict__ part,
-    int slot_in, double dt_fixed, FvChain chain, Ph ph)
+    const PatchDev *__restrict__ patches, FvPlan plan, Ctrl *__restrict__ ctrl, int slot_in, double dt_fixed, FvChain chain, Ph ph)
 {
     constexpr int N = Ph::N, A = Ph::A, AP = PlaneAux<Ph>::n, W = N + AP, AA = A > 0 ? A : 1;
     constexpr int PH = kFvPmax + 2;
@@ -394,8 +392,7 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
         const int z1 = (DIM == 3) ? min(p, z0 + plan.slab) : 1;
         segment(k, min(z0, z1), max(0, z1 - z0));
     }
-    if (__syncthreads_or(bad) && t == 0) atomicAdd(&ctrl->nonfinite, 1ull);
-    if (kLam) fold_speeds<DIM>(ctrl, part, lm, unit, plan.n_units, chain);
+    finish_step<DIM, kLam>(ctrl, slot_in, dt, lm, bad, chain);
 }
 
 // ---------------------------------------------------------------------------
@@ -495,8 +492,7 @@ __device__ __forceinline__ void dma_plane(void *buf_v, const void *q_v, int esz,
 template <class Ph, typename T, bool kLam>
 __global__ __launch_bounds__(kFvThreads, 2) void fv_step_dma_kernel(
     const T *__restrict__ qin, T *__restrict__ qout, const PatchDev *__restrict__ patches, int n_units,
-    int n_slabs, int slab, int remap, Ctrl *__restrict__ ctrl, double *__restrict__ part, int slot_in,
-    double dt_fixed, FvChain chain, Ph ph)
+    int n_slabs, int slab, int remap, Ctrl *__restrict__ ctrl, int slot_in, double dt_fixed, FvChain chain, Ph ph)
 {
     constexpr int N = Ph::N, A = Ph::A, AA = A > 0 ? A : 1;
     static_assert(Ph::E == 0, "the DMA variant has no extra per-cell input");
@@ -671,8 +667,7 @@ __global__ __launch_bounds__(kFvThreads, 2) void fv_step_dma_kernel(
         // no DMA may still write LDS when the work-group ends
         wait_vm(0);
     }
-    if (__syncthreads_or(bad) && t == 0) atomicAdd(&ctrl->nonfinite, 1ull);
-    if (kLam) fold_speeds<3>(ctrl, part, lm, unit, n_units, chain);
+    finish_step<3, kLam>(ctrl, slot_in, dt, lm, bad, chain);
 }
 
 // ---------------------------------------------------------------------------
@@ -690,8 +685,7 @@ __global__ __launch_bounds__(kFvThreads, 2) void fv_step_dma_kernel(
 template <class Ph, typename T, bool kLam>
 __global__ __launch_bounds__(kFvThreads) void fv_small_kernel(
     const T *__restrict__ qin, T *__restrict__ qout, const double *__restrict__ ex,
-    const PatchDev *__restrict__ patches, int K, int p, int G, Ctrl *__restrict__ ctrl,
-    double *__restrict__ part, int slot_in, double dt_fixed, FvChain chain, Ph ph)
+    const PatchDev *__restrict__ patches, int K, int p, int G, Ctrl *__restrict__ ctrl, int slot_in, double dt_fixed, FvChain chain, Ph ph)
 {
     constexpr int N = Ph::N, A = Ph::A, AA = A > 0 ? A : 1;
     extern __shared__ double box[];   // [N + A][G * B]
@@ -777,30 +771,38 @@ __global__ __launch_bounds__(kFvThreads) void fv_small_kernel(
         }
         if (kLam) cell_speeds_fast<Ph, 3>(ph, qw, lm);
     }
-    if (__syncthreads_or(bad) && t == 0) atomicAdd(&ctrl->nonfinite, 1ull);
-    if (kLam) fold_speeds<3>(ctrl, part, lm, blockIdx.x, gridDim.x, chain);
+    finish_step<3, kLam>(ctrl, slot_in, dt, lm, bad, chain);
 }
 
 // Largest speeds of the current state (first step of a call in CFL mode):
-// one work-group per patch, partial maxima per patch.
+// work-group u takes patches u, u + gridDim.x, ... and stores its maxima as
+// partials; work-group 0 clears slot 0 of the hand-over lines.
 template <class Ph, int DIM, typename T>
 __global__ __launch_bounds__(kFvThreads) void fv_lambda_kernel(const T *__restrict__ q,
-                                                               const PatchDev *__restrict__ patches,
-                                                               double *__restrict__ part, Ph ph)
+                                                               const PatchDev *__restrict__ patches, int K,
+                                                               double *__restrict__ part,
+                                                               unsigned long long *__restrict__ lines, int n_lines,
+                                                               Ph ph)
 {
     constexpr int N = Ph::N, A = Ph::A;
-    const PatchDev P = patches[blockIdx.x];
-    const int p = P.p;
-    const long long C = (DIM == 3) ? (long long)p * p * p : (long long)p * p;
     double lm[3] = {0.0, 0.0, 0.0};
     double e[1] = {0.0};
-    for (long long c = threadIdx.x; c < C; c += blockDim.x) {
-        double qc[N], ac[A > 0 ? A : 1];
-        load_cell<Ph>(q, (const double *)nullptr, P.off, C, c, qc, e);
-        ph.aux(qc, e, ac);
-        cell_speeds<Ph, DIM>(ph, qc, ac, lm);
+    for (int k = blockIdx.x; k < K; k += gridDim.x) {
+        const PatchDev &P = patches[k];
+        const int p = P.p;
+        const long long C = (DIM == 3) ? (long long)p * p * p : (long long)p * p;
+        for (long long c = threadIdx.x; c < C; c += blockDim.x) {
+            double qc[N], ac[A > 0 ? A : 1];
+            load_cell<Ph>(q, (const double *)nullptr, P.off, C, c, qc, e);
+            ph.aux(qc, e, ac);
+            cell_speeds<Ph, DIM>(ph, qc, ac, lm);
+        }
     }
     store_partial<DIM>(part, lm, blockIdx.x, gridDim.x);
+    if (blockIdx.x == 0 && (int)threadIdx.x < n_lines) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) lines[16 * threadIdx.x + d] = 0ull;
+    }
 }
 
 // dt from the partial maxima: Lambda_d = max over units, then
@@ -855,8 +857,6 @@ __global__ __launch_bounds__(1024) void dt_reduce_kernel(const double *__restric
             const double dt = cfl / den;
             ctrl->dt[slot] = dt;
             ctrl->last_dt = dt;
-            // the first FV step of a call folds its speeds into lmax[0]
-            for (int d = 0; d < 3; ++d) ctrl->lmax[0][d] = 0ull;
         }
         if (want_stats) {
             ctrl->c2p_iters += (unsigned long long)tot[3];
@@ -933,16 +933,14 @@ template <class Ph, int DIM, typename T>
 pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, int slot_in, int step,
                        double dt_fixed, double cfl, hipStream_t s)
 {
-    // in CFL mode the steps of a call hand the speed maxima to each other
-    // through the control block (FvChain); step < 0 stores partials and
-    // runs the reduction kernel after the step
-    const FvChain chain{step, cfl, b->dxmin};
     const int slab = (DIM == 3) ? (b->fv_slab > 0 ? std::min(b->fv_slab, b->pmax) : b->pmax) : 1;
     const int n_slabs = (DIM == 3) ? (b->pmax + slab - 1) / slab : 1;
     int n_units = b->K * n_slabs;
     Ctrl *ctrl = reinterpret_cast<Ctrl *>(b->ws);
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
-    double *part = reinterpret_cast<double *>(b->ws + L.part);
+    // in CFL mode the steps of a call hand the speed maxima to each other
+    const FvChain chain{step, cfl, b->dxmin, reinterpret_cast<unsigned long long *>(b->ws + L.lines), L.n_lines,
+                        reinterpret_cast<const double *>(b->ws + L.part), std::min(b->K, kLamUnits)};
     const T *qi = static_cast<const T *>(qin);
     T *qo = static_cast<T *>(qout);
     const double *ex = Ph::E ? reinterpret_cast<const double *>(b->ws + L.pres)
@@ -957,12 +955,11 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
         const bool lam = !(dt_fixed > 0.0) && Ph::E == 0;
         if (lam)
             launch_main(b, fv_small_kernel<Ph, T, true>, dim3(nwg), dim3(kFvThreads), lds, s, qi, qo, ex,
-                               b->d_patches, b->K, p, G, ctrl, part, slot_in, dt_fixed, chain, ph);
+                               b->d_patches, b->K, p, G, ctrl, slot_in, dt_fixed, chain, ph);
         else
             launch_main(b, fv_small_kernel<Ph, T, false>, dim3(nwg), dim3(kFvThreads), lds, s, qi, qo, ex,
-                               b->d_patches, b->K, p, G, ctrl, part, slot_in, dt_fixed, chain, ph);
+                               b->d_patches, b->K, p, G, ctrl, slot_in, dt_fixed, chain, ph);
         PB_HIP(hipGetLastError());
-        if (lam && step < 0) return launch_dt_reduce(b, part, nwg, DIM, slot_in ^ 1, cfl, true, false, s);
         return PB_OK;
       }
     }
@@ -984,7 +981,7 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
             plan.n_units = (int)std::min<long long>(slots, planes);
         }
         n_units = plan.n_units;
-        launch_main(b, kern, dim3(plan.n_units), dim3(kFvThreads), 0, s, qi, qo, ex, b->d_patches, plan, ctrl, part,
+        launch_main(b, kern, dim3(plan.n_units), dim3(kFvThreads), 0, s, qi, qo, ex, b->d_patches, plan, ctrl,
                     slot_in, dt_fixed, chain, ph);
         return PB_OK;
     };
@@ -994,11 +991,11 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
     } else if (DIM == 3 && b->fv_dma && fv_dma_eligible(b)) {
         if (dt_fixed > 0.0)
             launch_main(b, fv_step_dma_kernel<Ph, T, false>, dim3(n_units), dim3(kFvThreads), 0, s, qi, qo,
-                               b->d_patches, n_units, n_slabs, slab, b->fv_xcd_remap, ctrl, part, slot_in, dt_fixed,
+                               b->d_patches, n_units, n_slabs, slab, b->fv_xcd_remap, ctrl, slot_in, dt_fixed,
                                chain, ph);
         else
             launch_main(b, fv_step_dma_kernel<Ph, T, true>, dim3(n_units), dim3(kFvThreads), 0, s, qi, qo,
-                               b->d_patches, n_units, n_slabs, slab, b->fv_xcd_remap, ctrl, part, slot_in, dt_fixed,
+                               b->d_patches, n_units, n_slabs, slab, b->fv_xcd_remap, ctrl, slot_in, dt_fixed,
                                chain, ph);
     } else {
         if (dt_fixed > 0.0)
@@ -1008,24 +1005,20 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
     }
     if (lst != PB_OK) return lst;
     PB_HIP(hipGetLastError());
-    if (!(dt_fixed > 0.0) && Ph::E == 0 && step < 0) {
-        pb_status st = launch_dt_reduce(b, part, n_units, DIM, slot_in ^ 1, cfl, true, false, s);
-        if (st != PB_OK) return st;
-    }
     return PB_OK;
 }
 
 template <class Ph, int DIM, typename T>
-pb_status launch_lambda_typed(pb_batch *b, const Ph &ph, const void *q, double cfl, hipStream_t s)
+pb_status launch_lambda_typed(pb_batch *b, const Ph &ph, const void *q, double cfl, bool reduce, hipStream_t s)
 {
-    Ctrl *ctrl = reinterpret_cast<Ctrl *>(b->ws);
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
     double *part = reinterpret_cast<double *>(b->ws + L.part);
-    hipLaunchKernelGGL((fv_lambda_kernel<Ph, DIM, T>), dim3(b->K), dim3(kFvThreads), 0, s,
-                       static_cast<const T *>(q), b->d_patches, part, ph);
+    const int units = std::min(b->K, kLamUnits);
+    hipLaunchKernelGGL((fv_lambda_kernel<Ph, DIM, T>), dim3(units), dim3(kFvThreads), 0, s, static_cast<const T *>(q),
+                       b->d_patches, b->K, part, reinterpret_cast<unsigned long long *>(b->ws + L.lines), L.n_lines,
+                       ph);
     PB_HIP(hipGetLastError());
-    (void)ctrl;
-    return launch_dt_reduce(b, part, b->K, DIM, 0, cfl, true, false, s);
+    return reduce ? launch_dt_reduce(b, part, units, DIM, 0, cfl, true, false, s) : PB_OK;
 }
 
 // dispatch on (pde, dim, storage); F is a generic lambda taking (phys, dim tag, T tag)
@@ -1219,7 +1212,7 @@ pb_status launch_fv_step(pb_batch *b, const void *qin, void *qout, int slot_in, 
     });
 }
 
-pb_status launch_fv_lambda(pb_batch *b, const void *q, double cfl, hipStream_t s)
+pb_status launch_fv_lambda(pb_batch *b, const void *q, double cfl, bool reduce, hipStream_t s)
 {
     return dispatch(b, [&](const auto &ph, auto dimc, auto tt) -> pb_status {
         using Ph = std::decay_t<decltype(ph)>;
@@ -1229,7 +1222,7 @@ pb_status launch_fv_lambda(pb_batch *b, const void *q, double cfl, hipStream_t s
             set_error("internal: SRHD speeds come from the con2prim pass");
             return PB_EINVAL;
         } else {
-            return launch_lambda_typed<Ph, DIM, T>(b, ph, q, cfl, s);
+            return launch_lambda_typed<Ph, DIM, T>(b, ph, q, cfl, reduce, s);
         }
     });
 }
