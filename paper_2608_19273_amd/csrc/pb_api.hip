@@ -340,6 +340,8 @@ pb_status patch_batch_create(const pb_batch_desc *d, pb_batch **out)
     b->total_cells = cells;
     b->dxmin = dxmin;
     b->pmax = pmax;
+    b->self = true;
+    for (size_t i = 0; i < b->nbr.size() && b->self; ++i) b->self = b->nbr[i] == (int)(i / (2 * d->dim));
     b->uniform_p = std::all_of(b->p.begin(), b->p.end(), [&](int v) { return v == b->p[0]; });
 
     std::vector<PatchDev> tab((size_t)b->K);

@@ -327,6 +327,7 @@ struct pb_batch {
     double dxmin = 0.0;
     int pmax = 0;
     bool uniform_p = true;
+    bool self = false;   // every patch is its own neighbour on every face
     pb::PatchDev *d_patches = nullptr;
     long long steps = 0;
     double last_dt_host = 0.0;

@@ -673,105 +673,198 @@ __global__ __launch_bounds__(kFvThreads, 2) void fv_step_dma_kernel(
 // ---------------------------------------------------------------------------
 // Small patches (3D, one p for the whole batch, p^3 <= 256).  The plane march
 // leaves most of a work-group idle when p^2 is small (9 of 256 threads for
-// p = 3).  Here a work-group takes G whole patches, one thread per cell:
-//   1. every thread stages its cell's Q and aux in an LDS box of (p+2)^3
-//      slots per patch (edges and corners unused), and the work-group stages
-//      the G * 6p^2 face-halo cells read from the neighbours (the halo
-//      gather, again fused into the load);
-//   2. after one barrier every thread evaluates the three directions in the
-//      difference form of the plane kernel from its six face neighbours,
-//      updates, stores and folds the speeds of the new state.
-// G = min(256 / p^3, 64 KB / box) is chosen by the launcher.
-template <class Ph, typename T, bool kLam>
-__global__ __launch_bounds__(kFvThreads) void fv_small_kernel(
-    const T *__restrict__ qin, T *__restrict__ qout, const double *__restrict__ ex,
-    const PatchDev *__restrict__ patches, int K, int p, int G, Ctrl *__restrict__ ctrl, int slot_in, double dt_fixed, FvChain chain, Ph ph)
-{
-    constexpr int N = Ph::N, A = Ph::A, AA = A > 0 ? A : 1;
-    extern __shared__ double box[];   // [N + A][G * B]
-    const int t = threadIdx.x;
-    const int P3 = p * p * p, pb = p + 2, B = pb * pb * pb, SL = G * B;
-    const int k0 = blockIdx.x * G;
-    const int g = t / P3, l = t - g * P3;
-    const bool active = g < G && k0 + g < K;
-    const int x = l % p, y = (l / p) % p, z = l / (p * p);
-    const double dt = step_dt<3, kLam>(ctrl, slot_in, dt_fixed, chain);
-    auto slot = [&](int gg, int xx, int yy, int zz) { return gg * B + ((zz + 1) * pb + (yy + 1)) * pb + (xx + 1); };
+// p = 3).  Here a work-group takes groups of G whole patches, one thread per
+// cell, and goes from group to group while the batch lasts:
+//   1. every thread puts its cell's Q and aux into LDS, and (kSelf false) the
+//      work-group does the same for the G * 6p^2 face-halo cells read from the
+//      neighbours (the halo gather, again fused into the load).  Slots: the
+//      G p^3 cells, then per patch and face the p^2 halo cells;
+//   2. the loads of the next group go out, and after one barrier every thread
+//      evaluates the three directions in the difference form of the plane
+//      kernel from its six face neighbours, updates, stores and keeps the
+//      speeds of the new state.
+// kSelf: every patch is periodic on itself, so a face neighbour is a cell of
+// the same patch in LDS: nothing is loaded or evaluated twice.  With one p the
+// patches lie one after the other, so the group gives every address but the
+// neighbours' indexes, which are loaded two groups ahead.
+// Bound: FP64 issue.  8694 patches of 6^3 (1.9 M cells, 150 MB): 36 us per
+// step with kSelf, 54 us (8000 of them) without, 24 us at the copy rate; one group per
+// work-group, halo cells loaded and evaluated in every case: 62 us.
+constexpr int kSmallHalo = 2;   // halo cells per thread, at most
 
-    double qc[N], ac[AA], e[1] = {0.0};
-    double inv_dx = 0.0;
-    const int s = slot(active ? g : 0, x, y, z);
-    if (active) {
-        const PatchDev P = patches[k0 + g];
-        inv_dx = P.inv_dx;
-        load_cell<Ph>(qin, ex, P.off, P3, l, qc, e);
-        ph.aux(qc, e, ac);
+// doubles per LDS slot: Q and aux of one cell side by side, so that a
+// neighbour's are immediate offsets of one address; odd, so that consecutive
+// slots start in different banks
+template <class Ph> constexpr int kSmallSlot = (Ph::N + Ph::A) | 1;
+
+// patches per group: as many as the threads, the halo loads and the LDS hold
+template <class Ph>
+int small_group(int p)
+{
+    const int box = (p + 2) * (p + 2) * (p + 2);
+    return std::max(1, std::min({kFvThreads / (p * p * p), kSmallHalo * kFvThreads / (6 * p * p),
+                                 (int)(kFvSmallLds / ((Ph::N + Ph::A) * box * sizeof(double)))}));
+}
+
+template <class Ph, typename T, bool kLam, bool kSelf>
+__global__ __launch_bounds__(kFvThreads, kSelf ? 4 : 3) void fv_small_kernel(
+    const T *__restrict__ qin, T *__restrict__ qout, const double *__restrict__ ex,
+    const PatchDev *__restrict__ patches, int K, int p, int G, int n_groups, Ctrl *__restrict__ ctrl, int slot_in,
+    double dt_fixed, FvChain chain, Ph ph)
+{
+    constexpr int N = Ph::N, A = Ph::A, AA = A > 0 ? A : 1, W = kFvThreads / kWave, SW = kSmallSlot<Ph>;
+    extern __shared__ double box[];   // [slots][SW]
+    __shared__ int sbad[2][W];
+    const int t = threadIdx.x;
+    const int P2 = p * p, P3 = P2 * p, HP = 6 * P2, NC = G * P3;
+    const int g = t / P3, l = t - g * P3;
+    const int x = l % p, y = (l / p) % p, z = l / P2;
+    const double dt = step_dt<3, kLam>(ctrl, slot_in, dt_fixed, chain);
+    const int grid = (int)gridDim.x, first = xcd_remap(blockIdx.x, grid);
+
+    // LDS slots of the six face neighbours (threads beyond the group's cells: slot 0)
+    int nb[6];
+    {
+        const int c[3] = {x, y, z}, st[3] = {1, p, P2};
 #pragma unroll
-        for (int v = 0; v < N; ++v) box[v * SL + s] = qc[v];
-#pragma unroll
-        for (int a = 0; a < A; ++a) box[(N + a) * SL + s] = ac[a];
+        for (int f = 0; f < 6; ++f) {
+            const int d = f >> 1, s = f & 1, e = s ? p - 1 : 0;
+            const int in = t + (s ? st[d] : -st[d]);
+            const int wrap = t + (s ? -(p - 1) : p - 1) * st[d];
+            const int ij = d == 0 ? z * p + y : d == 1 ? z * p + x : y * p + x;
+            nb[f] = c[d] != e ? in : kSelf ? wrap : NC + (g * 6 + f) * P2 + ij;
+            nb[f] = t < NC ? nb[f] * SW : 0;
+        }
     }
-    // face halos: face f = 2 dir + side of patch gg, position (i, j) on it
-    const int HF = p * p, HP = 6 * HF;
-    for (int h = t; h < G * HP; h += blockDim.x) {
-        const int gg = h / HP, r = h - gg * HP, f = r / HF, ij = r - f * HF, i = ij % p, j = ij / p;
-        if (k0 + gg >= K) break;   // h only grows, and so does gg
-        const int dir = f >> 1, side = f & 1;
-        const int nb = patches[k0 + gg].nbr[f];
-        const int at = side ? p : -1, from = side ? 0 : p - 1;
-        int dx_, dy_, dz_, sx, sy, sz;
-        if (dir == 0)      { dx_ = at; sx = from; dy_ = sy = i; dz_ = sz = j; }
-        else if (dir == 1) { dy_ = at; sy = from; dx_ = sx = i; dz_ = sz = j; }
-        else               { dz_ = at; sz = from; dx_ = sx = i; dy_ = sy = j; }
-        double hq[N], ha[AA], he[1] = {0.0};
-        load_cell<Ph>(qin, ex, patches[nb].off, P3, (sz * p + sy) * p + sx, hq, he);
-        ph.aux(hq, he, ha);
-        const int d = slot(gg, dx_, dy_, dz_);
+    // this thread's halo cells (the cell of slot NC + t + 256 k): group-local
+    // patch and face (index into the neighbour table), source cell
+    int hpf[kSmallHalo], hcell[kSmallHalo];
+    if (!kSelf) {
 #pragma unroll
-        for (int v = 0; v < N; ++v) box[v * SL + d] = hq[v];
-#pragma unroll
-        for (int a = 0; a < A; ++a) box[(N + a) * SL + d] = ha[a];
+        for (int k = 0; k < kSmallHalo; ++k) {
+            const int h = t + k * kFvThreads;
+            const int gg = h / HP, r = h - gg * HP, f = r / P2, ij = r - f * P2, i = ij % p, j = ij / p;
+            const int from = (f & 1) ? 0 : p - 1, d = f >> 1;
+            hpf[k] = h < G * HP ? gg * 8 + f : -1;
+            hcell[k] = d == 0 ? (j * p + i) * p + from : d == 1 ? (j * p + from) * p + i : (from * p + j) * p + i;
+        }
     }
-    lds_barrier();   // (no thread reads what another writes to global memory)
+    // the loads in flight: this thread's cell and halo cells of the next
+    // group, and the halo cells' source patches of the one after it.  Lanes
+    // without a cell load the group's first one (no load sits in a divergent
+    // branch).
+    RawCell<Ph, T> rc, rh[kSelf ? 1 : kSmallHalo];
+    int hn[kSmallHalo] = {0, 0};
+    double idx = 0.0, idn = 0.0;
+    auto load_nbr = [&](int grp) {
+        if (kSelf) return;
+#pragma unroll
+        for (int k = 0; k < kSmallHalo; ++k) {
+            const int gg = hpf[k] >> 3, f = hpf[k] & 7, kk = grp * G + gg;
+            hn[k] = patches[hpf[k] >= 0 && kk < K ? kk : 0].nbr[hpf[k] >= 0 ? f : 0];
+        }
+    };
+    auto load_group = [&](int grp) {
+        const int k = grp * G + g;
+        const bool on = t < NC && k < K;
+        const long long off = (long long)(on ? k : grp * G) * P3;
+        idn = patches[on ? k : grp * G].inv_dx;
+        issue_load<Ph>(qin, ex, off, P3, on ? l : 0, rc);
+        if (!kSelf) {
+#pragma unroll
+            for (int h = 0; h < kSmallHalo; ++h)
+                issue_load<Ph>(qin, ex, (long long)hn[h] * P3, P3, hpf[h] >= 0 ? hcell[h] : 0, rh[h]);
+        }
+    };
 
     double lm[3] = {0.0, 0.0, 0.0};
-    bool bad = false;
-    if (active) {
-        double acc2[N];
-#pragma unroll
-        for (int v = 0; v < N; ++v) acc2[v] = 0.0;
-        auto dirn = [&](auto D, int st) {
-            double qL[N], aL[AA], qR[N], aR[AA];
-#pragma unroll
-            for (int v = 0; v < N; ++v) { qL[v] = box[v * SL + s - st]; qR[v] = box[v * SL + s + st]; }
-#pragma unroll
-            for (int a = 0; a < A; ++a) { aL[a] = box[(N + a) * SL + s - st]; aR[a] = box[(N + a) * SL + s + st]; }
-            rusanov_pair2<Ph, decltype(D)::value>(ph, qL, aL, qc, ac, qR, aR, acc2);
-        };
-        dirn(std::integral_constant<int, 0>(), 1);
-        dirn(std::integral_constant<int, 1>(), pb);
-        dirn(std::integral_constant<int, 2>(), pb * pb);
-        double S[N];
-        if (Ph::kSrc) {
-            ph.source(qc, ac, S);
-        } else {
-#pragma unroll
-            for (int v = 0; v < N; ++v) S[v] = 0.0;
-        }
-        const double hr_ = 0.5 * dt * inv_dx;
-        const PatchDev P = patches[k0 + g];
-        T *dst = qout + P.off * N + l;
-        double qw[N];
-#pragma unroll
-        for (int v = 0; v < N; ++v) {
-            const T st = (T)(v < N - Ph::M ? qc[v] - hr_ * acc2[v] + dt * S[v] : qc[v]);
-            __builtin_nontemporal_store(st, dst + (long long)v * P3);
-            qw[v] = (double)st;
-            bad |= !isfinite(qw[v]);
-        }
-        if (kLam) cell_speeds_fast<Ph, 3>(ph, qw, lm);
+    int grp = first;
+    if (grp < n_groups) {
+        load_nbr(grp);
+        load_group(grp);
+        load_nbr(min(grp + grid, n_groups - 1));
     }
-    finish_step<3, kLam>(ctrl, slot_in, dt, lm, bad, chain);
+    for (int it = 0; grp < n_groups; grp += grid, it ^= 1) {
+        const int k = grp * G + g;
+        const bool active = t < NC && k < K;
+        double qc[N], ac[AA], e[1] = {0.0};
+        unpack<Ph>(rc, qc, e);
+        ph.aux(qc, e, ac);
+        idx = idn;
+        if (t < NC) {
+#pragma unroll
+            for (int v = 0; v < N; ++v) box[t * SW + v] = qc[v];
+#pragma unroll
+            for (int a = 0; a < A; ++a) box[t * SW + N + a] = ac[a];
+        }
+        if (!kSelf) {
+#pragma unroll
+            for (int h = 0; h < kSmallHalo; ++h) {
+                if (h * kFvThreads >= G * HP) continue;   // (the same for the whole work-group)
+                double hq[N], ha[AA], he[1] = {0.0};
+                unpack<Ph>(rh[h], hq, he);
+                ph.aux(hq, he, ha);
+                if (hpf[h] >= 0) {
+                    const int d = (NC + t + h * kFvThreads) * SW;
+#pragma unroll
+                    for (int v = 0; v < N; ++v) box[d + v] = hq[v];
+#pragma unroll
+                    for (int a = 0; a < A; ++a) box[d + N + a] = ha[a];
+                }
+            }
+        }
+        // (the last group is loaded again at the end, unused)
+        load_group(min(grp + grid, n_groups - 1));
+        load_nbr(min(grp + 2 * grid, n_groups - 1));
+        lds_barrier();   // (no thread reads what another writes to global memory)
+        bool bad = false;
+        if (active) {
+            double acc2[N];
+#pragma unroll
+            for (int v = 0; v < N; ++v) acc2[v] = 0.0;
+            auto dirn = [&](auto D, int sl, int sr) {
+                double qL[N], aL[AA], qR[N], aR[AA];
+#pragma unroll
+                for (int v = 0; v < N; ++v) { qL[v] = box[sl + v]; qR[v] = box[sr + v]; }
+#pragma unroll
+                for (int a = 0; a < A; ++a) { aL[a] = box[sl + N + a]; aR[a] = box[sr + N + a]; }
+                // (one direction's reads at a time: all of them would not fit the registers)
+                __builtin_amdgcn_sched_barrier(0);
+                rusanov_pair2<Ph, decltype(D)::value>(ph, qL, aL, qc, ac, qR, aR, acc2);
+            };
+            dirn(std::integral_constant<int, 0>(), nb[0], nb[1]);
+            dirn(std::integral_constant<int, 1>(), nb[2], nb[3]);
+            dirn(std::integral_constant<int, 2>(), nb[4], nb[5]);
+            double S[N];
+            if (Ph::kSrc) {
+                ph.source(qc, ac, S);
+            } else {
+#pragma unroll
+                for (int v = 0; v < N; ++v) S[v] = 0.0;
+            }
+            const double hr_ = 0.5 * dt * idx;
+            T *dst = qout + (long long)k * P3 * N + l;
+            double qw[N];
+#pragma unroll
+            for (int v = 0; v < N; ++v) {
+                const T st = (T)(v < N - Ph::M ? qc[v] - hr_ * acc2[v] + dt * S[v] : qc[v]);
+                __builtin_nontemporal_store(st, dst + (long long)v * P3);
+                qw[v] = (double)st;
+                bad |= !isfinite(qw[v]);
+            }
+            if (kLam) cell_speeds_fast<Ph, 3>(ph, qw, lm);
+        }
+        // groups with a NaN or infinity are counted one by one
+        const bool any = __ballot(bad) != 0;
+        if ((t & (kWave - 1)) == 0) sbad[it][t / kWave] = any;
+        lds_barrier();   // the group's LDS is free for the next one
+        if (t == 0) {
+            int b = 0;
+            for (int w = 0; w < W; ++w) b |= sbad[it][w];
+            if (b) atomicAdd(&ctrl->nonfinite, 1ull);
+        }
+    }
+    finish_step<3, kLam>(ctrl, slot_in, dt, lm, false, chain);
 }
 
 // Largest speeds of the current state (first step of a call in CFL mode):
@@ -947,18 +1040,27 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
                              : nullptr;
     if constexpr (DIM == 3) {
       if (fv_small_eligible(b)) {
-        const int p = b->p[0], box = (p + 2) * (p + 2) * (p + 2);
-        const int G = std::max(1, std::min(kFvThreads / (p * p * p),
-                                           (int)(kFvSmallLds / ((Ph::N + Ph::A) * box * sizeof(double)))));
-        const int nwg = (b->K + G - 1) / G;
-        const size_t lds = (size_t)(Ph::N + Ph::A) * G * (p + 2) * (p + 2) * (p + 2) * sizeof(double);
+        const int p = b->p[0], G = small_group<Ph>(p), n_groups = (b->K + G - 1) / G;
+        const size_t lds = (size_t)kSmallSlot<Ph> * G * (p * p * p + (b->self ? 0 : 6 * p * p)) * sizeof(double);
+        int cus = 0;
+        pb_status st = device_cus(&cus);
+        if (st != PB_OK) return st;
+        // work-groups that are resident at once (by registers four or three, or
+        // as many as the LDS holds)
+        const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(b->self ? 4 : 3, (size_t)160 * 1024 / (lds + 512)));
+        const int nwg = std::min(n_groups, per_cu * cus);
         const bool lam = !(dt_fixed > 0.0) && Ph::E == 0;
-        if (lam)
-            launch_main(b, fv_small_kernel<Ph, T, true>, dim3(nwg), dim3(kFvThreads), lds, s, qi, qo, ex,
-                               b->d_patches, b->K, p, G, ctrl, slot_in, dt_fixed, chain, ph);
-        else
-            launch_main(b, fv_small_kernel<Ph, T, false>, dim3(nwg), dim3(kFvThreads), lds, s, qi, qo, ex,
-                               b->d_patches, b->K, p, G, ctrl, slot_in, dt_fixed, chain, ph);
+        auto go = [&](auto kern) {
+            launch_main(b, kern, dim3(nwg), dim3(kFvThreads), lds, s, qi, qo, ex, b->d_patches, b->K, p, G, n_groups,
+                        ctrl, slot_in, dt_fixed, chain, ph);
+        };
+        if constexpr (Ph::E > 0) {   // SRHD: dt comes from the con2prim pass
+            b->self ? go(fv_small_kernel<Ph, T, false, true>) : go(fv_small_kernel<Ph, T, false, false>);
+        } else if (b->self) {
+            lam ? go(fv_small_kernel<Ph, T, true, true>) : go(fv_small_kernel<Ph, T, false, true>);
+        } else {
+            lam ? go(fv_small_kernel<Ph, T, true, false>) : go(fv_small_kernel<Ph, T, false, false>);
+        }
         PB_HIP(hipGetLastError());
         return PB_OK;
       }
