@@ -203,7 +203,7 @@ static pb_status enqueue_fv(pb_batch *b, double cfl, double dt_fixed, int n, hip
     pb_status st;
     const bool cfl_mode = !(dt_fixed > 0.0);
     if (cfl_mode && b->pde != PB_PDE_SRHD)
-        if ((st = launch_fv_lambda(b, b->state[cur], cfl, false, s)) != PB_OK) return st;
+        if ((st = launch_fv_lambda(b, b->state[cur], s)) != PB_OK) return st;
     // span mode: without the con2prim pass the n step launches follow each
     // other with nothing in between, so one pair brackets all of them
     const bool span = b->prof_span && b->pde != PB_PDE_SRHD;
@@ -242,9 +242,9 @@ static pb_status enqueue_fd(pb_batch *b, double cfl, double dt_fixed, double sig
     void *yA = b->ws + L.yA, *yB = b->ws + L.yB;
     const bool euler = b->pde == PB_PDE_EULER;
     // Euler: dt on the device, from Q^n for the first step, then from the last
-    // stage of each step (ping-pong slots as in the FV path)
+    // stage of each step (handed over as in the FV path)
     if (euler && !(dt_fixed > 0.0))
-        if ((st = launch_fv_lambda(b, b->state[cur], cfl, true, s)) != PB_OK) return st;
+        if ((st = launch_fv_lambda(b, b->state[cur], s)) != PB_OK) return st;
     const double dt = euler ? 0.0 : fd_dt(b, cfl, dt_fixed);
     for (int i = 0; i < n; ++i) {
         // stage 1 reads Q^n, stages 2-4 the previous stage value: y1 in the
@@ -252,9 +252,16 @@ static pb_status enqueue_fd(pb_batch *b, double cfl, double dt_fixed, double sig
         // y2 and y3 in the workspace
         void *q0 = b->state[cur], *q1 = b->state[cur ^ 1];
         void *yin[4] = {q0, q1, yA, yB}, *yout[4] = {q1, yA, yB, q1};
+        if (euler && fd_self_eligible(b)) {
+            arm_events(b);
+            st = disarm_events(b, launch_fd_euler_self(b, rk, q0, q1, i, dt_fixed, cfl, sigma, s));
+            if (st != PB_OK) return st;
+            cur ^= 1;
+            continue;
+        }
         for (int sg = 0; sg < (rk == 1 ? 1 : 4); ++sg) {
             arm_events(b);
-            st = euler ? launch_fd_euler_stage(b, sg, rk, q0, yin[sg], q1, yA, yout[sg], i & 1, dt_fixed, cfl, sigma, s)
+            st = euler ? launch_fd_euler_stage(b, sg, rk, q0, yin[sg], q1, yA, yout[sg], i, dt_fixed, cfl, sigma, s)
                        : launch_fd_stage(b, sg, rk, q0, yin[sg], q1, yA, yout[sg], dt, sigma, s);
             if ((st = disarm_events(b, st)) != PB_OK) return st;
         }

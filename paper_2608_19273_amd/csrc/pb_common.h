@@ -428,9 +428,12 @@ inline void launch_main(const pb_batch *b, void (*kern)(P...), dim3 grid, dim3 b
 }
 
 // launchers (implemented in the kernel translation units)
-// largest speeds of state q: partials for the first step of an FV call, or
-// (reduce) reduced to dt in ctrl->dt[0]
-pb_status launch_fv_lambda(pb_batch *b, const void *q, double cfl, bool reduce, hipStream_t s);
+// largest speeds of state q: partials for the first step of a call
+pb_status launch_fv_lambda(pb_batch *b, const void *q, hipStream_t s);
+// the hand-over of the batch for step `step` of a call
+FvChain fv_chain(const pb_batch *b, int step, double cfl);
+// compute units of the current device
+pb_status device_cus(int *out);
 pb_status launch_fv_step(pb_batch *b, const void *qin, void *qout, int slot_in, int step, double dt_fixed,
                          double cfl, hipStream_t s);
 pb_status launch_srhd_c2p(pb_batch *b, const void *q, int slot_out, bool want_dt, double cfl,
@@ -440,12 +443,17 @@ pb_status launch_srhd_c2p(pb_batch *b, const void *q, int slot_out, bool want_dt
 // values y1 and y2, and out may be y1
 pb_status launch_fd_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, const void *y1,
                           const void *y2, void *out, double dt, double sigma, hipStream_t s);
-// one stage of the Euler FD4 + KO6 step, with the buffers of launch_fd_stage
-// (dt from ctrl->dt[slot] unless dt_fixed > 0; the last stage writes the next
-// step's dt to slot ^ 1)
+// one stage of step `step` of a call of the Euler FD4 + KO6 scheme, with the
+// buffers of launch_fd_stage (dt handed from step to step as in the FV path
+// unless dt_fixed > 0)
 pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, const void *y1,
-                                const void *y2, void *out, int slot, double dt_fixed, double cfl, double sigma,
+                                const void *y2, void *out, int step, double dt_fixed, double cfl, double sigma,
                                 hipStream_t s);
+// the whole step in one launch, where every patch is its own neighbour and
+// p^3 <= 256
+bool fd_self_eligible(const pb_batch *b);
+pb_status launch_fd_euler_self(pb_batch *b, int rk_stages, const void *q0, void *out, int step, double dt_fixed,
+                               double cfl, double sigma, hipStream_t s);
 // the DMA-fed FV kernel applies to this batch (3D, no extra per-cell input,
 // every p a multiple of 4, 16-byte aligned state buffers)
 bool fv_dma_eligible(const pb_batch *b);

@@ -33,7 +33,7 @@
 //      the halo ring, two work-groups per CU), applies the RK stage update
 //      and stores.
 // The last stage of a step also folds the largest characteristic speeds of
-// the new state into per-unit partials for the next step's dt, and counts
+// the new state into the hand-over to the next step's dt, and counts
 // non-finite results.
 #include <algorithm>
 
@@ -117,6 +117,16 @@ __device__ __forceinline__ void load5u_nt(const double *__restrict__ base, unsig
     for (int v = 0; v < kEN; ++v) out[v] = __builtin_nontemporal_load(at(base + (size_t)v * C, ob));
 }
 
+// a stage's dt: fixed; from the hand-over in a step's first stage, which
+// records it; from that record in the stages after it
+template <int S>
+__device__ __forceinline__ double stage_dt(const Ctrl *ctrl, int slot, double dt_fixed, const FvChain &chain)
+{
+    if (dt_fixed > 0.0) return dt_fixed;
+    if (S == 0 || S == 4) return step_dt<3, true>(ctrl, slot, dt_fixed, chain);
+    return ctrl->dt[slot];
+}
+
 }  // namespace
 
 // S: RK4 stage 0..3, or 4 for the single forward-Euler stage (rk_base has the
@@ -131,8 +141,9 @@ __device__ __forceinline__ void load5u_nt(const double *__restrict__ base, unsig
 // rate), memory in stage 3 (350 us for 5 arrays and the halo strips).  With a
 // running sum of the k the stages moved 3, 5, 5 and 3 arrays in 291, 342, 346
 // and 298 us.
-// The final stages (3 and 4) fold the speeds of the new state into partials,
-// with a fixed dt too, where nobody reads them: without that code the compiler
+// The final stages (3 and 4) fold the speeds of the new state into the
+// hand-over to the next step (FvChain), with a fixed dt too, where nobody reads
+// them: without that code the compiler
 // orders the stage so that it spills 37 registers (two steps of 2048 16^3
 // patches with a fixed dt: 2102 us without it, 1927 us with it).
 // runs (non-null): unit u marches runs[u] = (patch, first plane, planes, 0)
@@ -143,8 +154,8 @@ template <int S>
 __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
     const double *__restrict__ y, const double *__restrict__ q0, const double *y1, const double *__restrict__ y2,
     double *out, const PatchDev *__restrict__ patches, int n_units, int n_slabs, int slab, int remap,
-    const int4 *__restrict__ runs, Ctrl *__restrict__ ctrl, double *__restrict__ part, int slot, double dt_fixed,
-    double gamma, double sigma)
+    const int4 *__restrict__ runs, Ctrl *__restrict__ ctrl, FvChain chain, int slot, double dt_fixed, double gamma,
+    double sigma)
 {
     constexpr int N = kEN;
     constexpr bool kReadQ0 = S == 1 || S == 2 || S == 3;
@@ -184,7 +195,7 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
     const bool active = work && t < p * p;
     const int x = active ? t % p : 0, yy = active ? t / p : 0;
     const unsigned cxy = (unsigned)(yy * p + x), cxy8 = 8u * cxy;
-    const double dt = dt_fixed > 0.0 ? dt_fixed : ctrl->dt[slot];
+    const double dt = stage_dt<S>(ctrl, slot, dt_fixed, chain);
     const double ca = S == 2 || S == 4 ? dt : S == 3 ? dt / 6.0 : 0.5 * dt;
     const double gm1 = gamma - 1.0;
     double c4 = inv_dx / 12.0, cko = sigma * inv_dx / 64.0;
@@ -434,10 +445,8 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
         plane(std::integral_constant<int, 6>());
         ++i;
     }
-    if (kFinal) {
-        if (__syncthreads_or(bad) && t == 0) atomicAdd(&ctrl->nonfinite, 1ull);
-        store_partial<3>(part, lm, unit, n_units);
-    }
+    if (kFinal) finish_step<3, true>(ctrl, slot, dt, lm, bad, chain);
+    if (S == 0 && blockIdx.x == 0 && t == 0) ctrl->dt[slot] = dt;
 }
 
 // ---------------------------------------------------------------------------
@@ -477,7 +486,7 @@ template <int S>
 __global__ __launch_bounds__(kFvThreads) void fd_euler_small_kernel(
     const double *__restrict__ y, const double *__restrict__ q0, const double *y1, const double *__restrict__ y2,
     double *out, const PatchDev *__restrict__ patches, int K, int p, int G, Ctrl *__restrict__ ctrl,
-    double *__restrict__ part, int slot, double dt_fixed, double gamma, double sigma)
+    FvChain chain, int slot, double dt_fixed, double gamma, double sigma)
 {
     constexpr int N = kEN;
     constexpr bool kReadQ0 = S == 1 || S == 2 || S == 3;
@@ -490,7 +499,7 @@ __global__ __launch_bounds__(kFvThreads) void fd_euler_small_kernel(
     const int g = t / geo.p3, l = t - g * geo.p3;
     const bool active = g < G && k0 + g < K;
     const int x = l % p, yy = (l / p) % p, z = l / geo.p2;
-    const double dt = dt_fixed > 0.0 ? dt_fixed : ctrl->dt[slot];
+    const double dt = stage_dt<S>(ctrl, slot, dt_fixed, chain);
     const double ca = S == 2 || S == 4 ? dt : S == 3 ? dt / 6.0 : 0.5 * dt;
     const double gm1 = gamma - 1.0;
     const Euler<3> ph{gamma};
@@ -607,10 +616,170 @@ __global__ __launch_bounds__(kFvThreads) void fd_euler_small_kernel(
             lm[2] = fmax(lm[2], ph.eig<2>(nv, a));
         }
     }
-    if (kFinal) {
-        if (__syncthreads_or(bad) && t == 0) atomicAdd(&ctrl->nonfinite, 1ull);
-        store_partial<3>(part, lm, blockIdx.x, gridDim.x);
+    if (kFinal) finish_step<3, true>(ctrl, slot, dt, lm, bad, chain);
+    if (S == 0 && blockIdx.x == 0 && t == 0) ctrl->dt[slot] = dt;
+}
+
+// ---------------------------------------------------------------------------
+// Small patches that are their own neighbours on every face: a patch's whole
+// RK4 step (STAGES = 4; 1: the forward-Euler stage) needs no other patch, so
+// it runs in one launch with the stage values in registers and the stage input
+// in LDS.  One thread per cell, G patches per work-group, work-groups going
+// from group to group with the next group's cells in flight.  The state is
+// read and written once per step, against 13 passes and four launches.
+// The arithmetic is the small-patch stage kernel's.
+// Bound: FP64 issue.  1024 patches of 6^3: 25 us per step, against four
+// stages of 15 us.
+constexpr int kSelfPerCu = 3;   // work-groups resident at once (by registers)
+
+template <int STAGES>
+__global__ __launch_bounds__(kFvThreads, kSelfPerCu) void fd_euler_self_kernel(
+    const double *__restrict__ q0, double *__restrict__ out, const PatchDev *__restrict__ patches, int K, int p, int G,
+    int n_groups, Ctrl *__restrict__ ctrl, FvChain chain, int slot, double dt_fixed, double gamma, double sigma)
+{
+    constexpr int N = kEN, W = kFvThreads / kWave;
+    extern __shared__ double sm[];   // [G p^3][kSmallW]
+    // Q^n, y1 and y2 of each thread's cell (its own slots only): in registers
+    // they would spill
+    __shared__ double park[STAGES == 1 ? 1 : 3][N][kFvThreads];
+    __shared__ int sbad[2][W];
+    const int t = threadIdx.x, p2 = p * p, p3 = p2 * p, NC = G * p3;
+    const int g = t / p3, l = t - g * p3;
+    const int c[3] = {l % p, (l / p) % p, l / p2}, st[3] = {1, p, p2};
+    // LDS slots of the stencil neighbours at -3, -2, -1, +1, +2, +3 (p >= 3)
+    int nb[3][6];
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const int v = c[d] + (k < 3 ? k - 3 : k - 2), w = v < 0 ? v + p : v >= p ? v - p : v;
+            nb[d][k] = t < NC ? (t + (w - c[d]) * st[d]) * kSmallW : 0;
+        }
+    const double dt = dt_fixed > 0.0 ? dt_fixed : step_dt<3, true>(ctrl, slot, dt_fixed, chain);
+    const double gm1 = gamma - 1.0;
+    const Euler<3> ph{gamma};
+    const unsigned C = (unsigned)p3;
+
+    double ql[N], idl = 0.0;   // the next group's cell and 1/dx
+    auto load_group = [&](int grp) {
+        const int k = grp * G + g;
+        const bool on = t < NC && k < K;   // (the others load the group's first cell)
+        const int kk = on ? k : grp * G;
+        idl = patches[kk].inv_dx;
+        load5(q0 + (long long)kk * p3 * N, on ? (unsigned)l : 0u, C, ql);
+    };
+    double lm[3] = {0.0, 0.0, 0.0};
+    const int grid = (int)gridDim.x;
+    int grp = blockIdx.x;   // (the grid is no larger than the list)
+    load_group(grp);
+    for (int it = 0; grp < n_groups; grp += grid, it ^= 1) {
+        const int k = grp * G + g;
+        const bool active = t < NC && k < K;
+        double qc[N];
+#pragma unroll
+        for (int v = 0; v < N; ++v) park[0][v][t] = qc[v] = ql[v];
+        const double c4 = idl / 12.0, cko = sigma * idl / 64.0;
+        load_group(min(grp + grid, n_groups - 1));
+        auto stage = [&](auto SC) __attribute__((always_inline)) {
+            constexpr int S = decltype(SC)::value;
+            double a[2];
+            euler_ip(qc, gm1, a);
+            if (t < NC) {
+#pragma unroll
+                for (int v = 0; v < N; ++v) sm[t * kSmallW + v] = qc[v];
+                sm[t * kSmallW + 5] = a[0];
+                sm[t * kSmallW + 6] = a[1];
+            }
+            lds_barrier();
+            double R[N], kox[N];
+#pragma unroll
+            for (int v = 0; v < N; ++v) { R[v] = 0.0; kox[v] = 0.0; }
+            auto dir = [&](auto D) {
+                constexpr int d = decltype(D)::value;
+                // outwards in: sums and differences of the pairs at 3, 2, 1
+                // (one pair's values at a time)
+                double s3[N], s2[N], f2[N];
+                auto cell = [&](int k, double *q, double *F) {
+                    const double *sl = sm + nb[d][k];
+                    double aa[2];
+#pragma unroll
+                    for (int v = 0; v < N; ++v) q[v] = sl[v];
+                    aa[0] = sl[5];
+                    aa[1] = sl[6];
+                    ph.flux<d>(q, aa, F);
+                };
+                double qm[N], qp[N], Fm[N], Fp[N];
+#pragma unroll
+                for (int v = 0; v < N; ++v) s3[v] = sm[nb[d][0] + v] + sm[nb[d][5] + v];
+                cell(1, qm, Fm);
+                cell(4, qp, Fp);
+#pragma unroll
+                for (int v = 0; v < N; ++v) {
+                    s2[v] = qm[v] + qp[v];
+                    f2[v] = Fm[v] - Fp[v];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                cell(2, qm, Fm);
+                cell(3, qp, Fp);
+#pragma unroll
+                for (int v = 0; v < N; ++v) {
+                    R[v] += f2[v] + 8.0 * (Fp[v] - Fm[v]);
+                    kox[v] += ((s3[v] - 6.0 * s2[v]) + 15.0 * (qm[v] + qp[v])) - 20.0 * qc[v];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            dir(std::integral_constant<int, 0>());
+            dir(std::integral_constant<int, 1>());
+            dir(std::integral_constant<int, 2>());
+            const double ca = S == 2 || S == 4 ? dt : S == 3 ? dt / 6.0 : 0.5 * dt;
+#pragma unroll
+            for (int v = 0; v < N; ++v) {
+                const double Rv = cko * kox[v] - c4 * R[v];
+                double base = park[0][v][t];
+                if constexpr (S == 3) base = rk_base(base, park[1][v][t], park[2][v][t], qc[v]);
+                qc[v] = base + ca * Rv;
+                if constexpr (S < 2) park[1 + S][v][t] = qc[v];
+                // (complete before the barrier: the compiler would move the
+                // arithmetic behind it and keep every stencil value until then)
+                __asm__ volatile("" : "+v"(qc[v]));
+            }
+            lds_barrier();   // the stage's LDS is free for the next one
+        };
+        if constexpr (STAGES == 1) {
+            stage(std::integral_constant<int, 4>());
+        } else {
+            stage(std::integral_constant<int, 0>());
+            stage(std::integral_constant<int, 1>());
+            stage(std::integral_constant<int, 2>());
+            stage(std::integral_constant<int, 3>());
+        }
+        bool bad = false;
+        if (active) {
+            double *o = out + (long long)k * p3 * N + l;
+#pragma unroll
+            for (int v = 0; v < N; ++v) {
+                o[(size_t)v * C] = qc[v];
+                bad |= !isfinite(qc[v]);
+            }
+            double a[3];
+            ph.aux_fast(qc, nullptr, a);
+            lm[0] = fmax(lm[0], ph.eig<0>(qc, a));
+            lm[1] = fmax(lm[1], ph.eig<1>(qc, a));
+            lm[2] = fmax(lm[2], ph.eig<2>(qc, a));
+        }
+        // groups with a NaN or infinity are counted one by one; the next
+        // group's barriers come before its flags go into the other set and
+        // the one after that into this one
+        const bool any = __ballot(bad) != 0;
+        if ((t & (kWave - 1)) == 0) sbad[it][t / kWave] = any;
+        lds_barrier();
+        if (t == 0) {
+            int b = 0;
+            for (int w = 0; w < W; ++w) b |= sbad[it][w];
+            if (b) atomicAdd(&ctrl->nonfinite, 1ull);
+        }
     }
+    finish_step<3, true>(ctrl, slot, dt, lm, false, chain);
 }
 
 // ------------------------------------------------------------------ host --
@@ -620,17 +789,17 @@ namespace {
 // G > 0: the small-patch kernel with G patches per work-group (n_units = work-groups)
 template <int S>
 void launch_s(dim3 g, hipStream_t s, const double *y, const double *q0, const double *y1, const double *y2, double *out,
-              const pb_batch *b, int n_units, int n_slabs, int slab, const int4 *runs, int G, Ctrl *ctrl, double *part, int slot,
-              double dt_fixed, double sigma)
+              const pb_batch *b, int n_units, int n_slabs, int slab, const int4 *runs, int G, Ctrl *ctrl,
+              const FvChain &chain, int slot, double dt_fixed, double sigma)
 {
     if (G > 0) {
         const int p = b->p[0];
         const size_t lds = (size_t)kSmallW * G * (p * p * p + 18 * p * p) * sizeof(double);
         launch_main(b, fd_euler_small_kernel<S>, g, dim3(kFvThreads), lds, s, y, q0, y1, y2, out,
-                           b->d_patches, b->K, p, G, ctrl, part, slot, dt_fixed, b->params[0], sigma);
+                           b->d_patches, b->K, p, G, ctrl, chain, slot, dt_fixed, b->params[0], sigma);
     } else {
         launch_main(b, fd_euler_stage_kernel<S>, g, dim3(kFvThreads), 0, s, y, q0, y1, y2, out, b->d_patches,
-                           n_units, n_slabs, slab, b->fd_xcd_remap, runs, ctrl, part, slot, dt_fixed, b->params[0],
+                           n_units, n_slabs, slab, b->fd_xcd_remap, runs, ctrl, chain, slot, dt_fixed, b->params[0],
                            sigma);
     }
 }
@@ -638,7 +807,7 @@ void launch_s(dim3 g, hipStream_t s, const double *y, const double *q0, const do
 }  // namespace
 
 pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const void *q0, const void *y, const void *y1,
-                                const void *y2, void *out, int slot, double dt_fixed, double cfl, double sigma,
+                                const void *y2, void *out, int step, double dt_fixed, double cfl, double sigma,
                                 hipStream_t s)
 {
     if (b->pmax > kFvPmax) { set_error("fd_ko_step: p > 16 is not supported for EULER"); return PB_EUNSUPPORTED; }
@@ -656,15 +825,14 @@ pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const voi
     const int4 *runs = (G == 0 && b->fd_column > 0 && b->fd_runs.d) ? static_cast<const int4 *>(b->fd_runs.d) : nullptr;
     const int n_units = G > 0 ? (b->K + G - 1) / G : runs ? b->fd_runs.n : b->K * n_slabs;
     Ctrl *ctrl = reinterpret_cast<Ctrl *>(b->ws);
-    const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
-    double *part = reinterpret_cast<double *>(b->ws + L.part);
+    const FvChain chain = fv_chain(b, step, cfl);
+    const int slot = step & 1;
     const int S = rk_stages == 1 ? 4 : stage;
-    const bool lam = (S == 3 || S == 4) && !(dt_fixed > 0.0);
     const double *yi = static_cast<const double *>(y), *q0i = static_cast<const double *>(q0);
     const double *y1i = static_cast<const double *>(y1), *y2i = static_cast<const double *>(y2);
     double *o = static_cast<double *>(out);
     const dim3 g(n_units);
-#define PB_FDE_ARGS g, s, yi, q0i, y1i, y2i, o, b, n_units, n_slabs, slab, runs, G, ctrl, part, slot, dt_fixed, sigma
+#define PB_FDE_ARGS g, s, yi, q0i, y1i, y2i, o, b, n_units, n_slabs, slab, runs, G, ctrl, chain, slot, dt_fixed, sigma
     switch (S) {
     case 0: launch_s<0>(PB_FDE_ARGS); break;
     case 1: launch_s<1>(PB_FDE_ARGS); break;
@@ -674,7 +842,33 @@ pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const voi
     }
 #undef PB_FDE_ARGS
     PB_HIP(hipGetLastError());
-    if (lam) return launch_dt_reduce(b, part, n_units, 3, slot ^ 1, cfl, true, false, s);
+    return PB_OK;
+}
+
+bool fd_self_eligible(const pb_batch *b)
+{
+    return b->self && b->uniform_p && b->p[0] * b->p[0] * b->p[0] <= kFvThreads;
+}
+
+pb_status launch_fd_euler_self(pb_batch *b, int rk_stages, const void *q0, void *out, int step, double dt_fixed,
+                               double cfl, double sigma, hipStream_t s)
+{
+    const int p = b->p[0], p3 = p * p * p, G = kFvThreads / p3, n_groups = (b->K + G - 1) / G;
+    const size_t lds = (size_t)kSmallW * G * p3 * sizeof(double);
+    int cus = 0;
+    pb_status st = device_cus(&cus);
+    if (st != PB_OK) return st;
+    const int nwg = std::min(n_groups, kSelfPerCu * cus);
+    const double *q = static_cast<const double *>(q0);
+    double *o = static_cast<double *>(out);
+    Ctrl *ctrl = reinterpret_cast<Ctrl *>(b->ws);
+    const FvChain chain = fv_chain(b, step, cfl);
+    auto go = [&](auto kern) {
+        launch_main(b, kern, dim3(nwg), dim3(kFvThreads), lds, s, q, o, b->d_patches, b->K, p, G, n_groups, ctrl, chain,
+                    step & 1, dt_fixed, b->params[0], sigma);
+    };
+    rk_stages == 1 ? go(fd_euler_self_kernel<1>) : go(fd_euler_self_kernel<4>);
+    PB_HIP(hipGetLastError());
     return PB_OK;
 }
 

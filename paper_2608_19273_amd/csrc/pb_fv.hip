@@ -1003,9 +1003,7 @@ __global__ void ctrl_init_kernel(Ctrl *ctrl)
 
 // ------------------------------------------------------------------ host --
 
-namespace {
-
-// compute units of the current device (cached per device)
+// (cached per device)
 pb_status device_cus(int *out)
 {
     static std::mutex mu;
@@ -1022,6 +1020,15 @@ pb_status device_cus(int *out)
     return PB_OK;
 }
 
+FvChain fv_chain(const pb_batch *b, int step, double cfl)
+{
+    const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
+    return FvChain{step, cfl, b->dxmin, reinterpret_cast<unsigned long long *>(b->ws + L.lines), L.n_lines,
+                   reinterpret_cast<const double *>(b->ws + L.part), std::min(b->K, kLamUnits)};
+}
+
+namespace {
+
 template <class Ph, int DIM, typename T>
 pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, int slot_in, int step,
                        double dt_fixed, double cfl, hipStream_t s)
@@ -1032,8 +1039,7 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
     Ctrl *ctrl = reinterpret_cast<Ctrl *>(b->ws);
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
     // in CFL mode the steps of a call hand the speed maxima to each other
-    const FvChain chain{step, cfl, b->dxmin, reinterpret_cast<unsigned long long *>(b->ws + L.lines), L.n_lines,
-                        reinterpret_cast<const double *>(b->ws + L.part), std::min(b->K, kLamUnits)};
+    const FvChain chain = fv_chain(b, step, cfl);
     const T *qi = static_cast<const T *>(qin);
     T *qo = static_cast<T *>(qout);
     const double *ex = Ph::E ? reinterpret_cast<const double *>(b->ws + L.pres)
@@ -1111,7 +1117,7 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
 }
 
 template <class Ph, int DIM, typename T>
-pb_status launch_lambda_typed(pb_batch *b, const Ph &ph, const void *q, double cfl, bool reduce, hipStream_t s)
+pb_status launch_lambda_typed(pb_batch *b, const Ph &ph, const void *q, hipStream_t s)
 {
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
     double *part = reinterpret_cast<double *>(b->ws + L.part);
@@ -1120,7 +1126,7 @@ pb_status launch_lambda_typed(pb_batch *b, const Ph &ph, const void *q, double c
                        b->d_patches, b->K, part, reinterpret_cast<unsigned long long *>(b->ws + L.lines), L.n_lines,
                        ph);
     PB_HIP(hipGetLastError());
-    return reduce ? launch_dt_reduce(b, part, units, DIM, 0, cfl, true, false, s) : PB_OK;
+    return PB_OK;
 }
 
 // dispatch on (pde, dim, storage); F is a generic lambda taking (phys, dim tag, T tag)
@@ -1314,7 +1320,7 @@ pb_status launch_fv_step(pb_batch *b, const void *qin, void *qout, int slot_in, 
     });
 }
 
-pb_status launch_fv_lambda(pb_batch *b, const void *q, double cfl, bool reduce, hipStream_t s)
+pb_status launch_fv_lambda(pb_batch *b, const void *q, hipStream_t s)
 {
     return dispatch(b, [&](const auto &ph, auto dimc, auto tt) -> pb_status {
         using Ph = std::decay_t<decltype(ph)>;
@@ -1324,7 +1330,7 @@ pb_status launch_fv_lambda(pb_batch *b, const void *q, double cfl, bool reduce, 
             set_error("internal: SRHD speeds come from the con2prim pass");
             return PB_EINVAL;
         } else {
-            return launch_lambda_typed<Ph, DIM, T>(b, ph, q, cfl, reduce, s);
+            return launch_lambda_typed<Ph, DIM, T>(b, ph, q, s);
         }
     });
 }

@@ -224,9 +224,9 @@ pb_status pb_autotune(pb_batch *b, int32_t kind, double cfl, double dt_fixed, do
         if (b->pde == PB_PDE_SRHD)
             st = launch_srhd_c2p(b, b->state[b->cur], 0, cfl_mode, cfl, s);
         else if (cfl_mode)
-            st = launch_fv_lambda(b, b->state[b->cur], cfl, false, s);
+            st = launch_fv_lambda(b, b->state[b->cur], s);
     } else if (b->pde == PB_PDE_EULER && cfl_mode) {
-        st = launch_fv_lambda(b, b->state[b->cur], cfl, true, s);   // dt of Q^n into slot 0, as a step's start
+        st = launch_fv_lambda(b, b->state[b->cur], s);   // speeds of Q^n, as a call's start
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (st == PB_OK && hipEventCreate(&e0) != hipSuccess) st = hip_fail(hipErrorUnknown, "hipEventCreate");
