@@ -371,7 +371,11 @@ pb_status pb_stream_copy(const void *src, void *dst, size_t bytes, void *stream)
  * computed; the FV slab changes the order of a few additions at slab seams
  * (last-bit differences), the others change nothing in the results. */
 typedef struct {
-    int32_t fv_slab;          /* FV: z-planes per work-group (0 = whole patch) */
+    int32_t fv_slab;          /* FV: z-planes per work-group.  0 = the library's
+                                 own split (column runs as for fv_column = 3,
+                                 no more of them than the device holds at
+                                 once), the default; unused where another
+                                 field asks for a split */
     int32_t fv_xcd_remap;     /* FV: 1 = group consecutive patches per XCD */
     int32_t fd_xcd_remap;     /* FD: 1 = each XCD takes a contiguous run of tiles
                                  (the tiles of one patch share its L2) */
@@ -402,8 +406,8 @@ typedef struct {
                                  planes (patch after patch): with w no larger
                                  than the work-groups a CU holds at once there
                                  is no partly filled last round; fv_slab is
-                                 then unused.  0 = one work-group per slab
-                                 (fv_slab), the default.  Results differ from
+                                 then unused.  0 = off (fv_slab), the
+                                 default.  Results differ from
                                  slab mode only where a slab seam changes the
                                  order of additions. */
     int32_t fv_column;        /* FV 3D (register kernel): w in 1..8 = column
@@ -426,7 +430,9 @@ typedef struct {
                                  of one p >= 4; every run at least one whole
                                  patch long), about w work-groups per CU;
                                  0 = one work-group per patch.  Default 2
-                                 (the kernel holds two work-groups per CU).
+                                 (the kernel holds two work-groups per CU);
+                                 there, in a batch of fewer than two patches
+                                 per CU, the runs may be shorter than a patch.
                                  Results are bitwise those of fd_column = 0.
                                  Builds a small device table here (host call,
                                  PB_EHIP if that fails). */

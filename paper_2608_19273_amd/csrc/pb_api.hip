@@ -304,7 +304,7 @@ pb_status pb_column_runs(const pb_batch_desc *desc, int32_t kind, int32_t w, int
     if (desc->dim != 3) { set_error("column runs apply to 3D batches"); return PB_EINVAL; }
     if (kind != 0 && kind != 1) { set_error("kind must be 0 (FV) or 1 (Euler FD)"); return PB_EINVAL; }
     if (w < 1 || w > 8 || cus < 1) { set_error("need w in [1, 8] and cus >= 1"); return PB_EINVAL; }
-    const std::vector<int4> r = column_runs(kind, desc->n_patches, desc->p, desc->neighbor, w, cus);
+    const std::vector<int4> r = column_runs(kind, desc->n_patches, desc->p, desc->neighbor, w, cus, false);
     *n_runs = (int32_t)r.size();
     if ((int32_t)r.size() > max_runs) { set_error("runs buffer too small"); return PB_EINVAL; }
     for (size_t i = 0; i < r.size(); ++i) {

@@ -467,7 +467,7 @@ bool fv_small_eligible(const pb_batch *b);
 // kind 0 (FV): links between patches of one p >= 2, runs of any length;
 // kind 1 (Euler FD, halo 3): links between patches of one p >= 4, runs of
 // whole patches at least.
-std::vector<int4> column_runs(int kind, int K, const int *p, const int *nbr, int w, int cus);
+std::vector<int4> column_runs(int kind, int K, const int *p, const int *nbr, int w, int cus, bool fit);
 // (re)builds the column-run tables for b->fv_column and b->fd_column (a
 // table is freed when its w is 0 or does not apply); host call, done when
 // the batch is created and when its tuning is set, never inside a capture

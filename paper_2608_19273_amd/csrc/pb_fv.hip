@@ -1076,7 +1076,7 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
     // once (uniform p)
     FvPlan plan{n_units, n_slabs, slab, b->fv_xcd_remap, 0, nullptr};
     auto plane_kernel = [&](auto kern) -> pb_status {
-        if (DIM == 3 && b->fv_column > 0 && b->fv_runs.d) {
+        if (DIM == 3 && b->fv_runs.d) {   // (built for the current tuning only)
             plan.runs = static_cast<const int4 *>(b->fv_runs.d);
             plan.n_units = b->fv_runs.n;
         } else if (DIM == 3 && b->fv_persist > 0 && b->uniform_p) {
@@ -1191,7 +1191,11 @@ pb_status dispatch(pb_batch *b, F &&f)
 // chain gave each XCD every layer of fewer chains, two rows on the headline
 // grid, so half the y-halo strips came from other XCDs: HBM reads 1.48x
 // the algorithmic reads instead of 1.16x.)
-std::vector<int4> column_runs(int kind, int K, const int *p, const int *nbr, int w, int cus)
+//
+// The library's own split (`fit`; no tuning asks for another) gives a chain
+// its share rounded down, so that all runs are resident at once, and lets the
+// FD runs be shorter than a patch where whole patches leave CUs without work.
+std::vector<int4> column_runs(int kind, int K, const int *p, const int *nbr, int w, int cus, bool fit)
 {
     const int pmin = kind == 0 ? 2 : 4;
     std::vector<int> succ(K, -1), pred(K, -1);
@@ -1235,8 +1239,9 @@ std::vector<int4> column_runs(int kind, int K, const int *p, const int *nbr, int
         const std::vector<int> &c = chains[o.second];
         const int pc = p[c[0]];
         const long long planes = (long long)c.size() * pc;
-        const long long rmax = kind == 0 ? planes : (long long)c.size();
-        const long long r = std::max(1LL, std::min(rmax, std::llround(slots * (double)planes / (double)total)));
+        const long long rmax = kind == 0 || fit ? planes : (long long)c.size();
+        const double share = slots * (double)planes / (double)total;
+        const long long r = std::max(1LL, std::min(rmax, fit ? (long long)(share + 1e-9) : std::llround(share)));
         per.emplace_back();
         for (long long j = 0; j < r; ++j) {
             const long long s0 = j * planes / r, s1 = (j + 1) * planes / r;
@@ -1254,23 +1259,24 @@ std::vector<int4> column_runs(int kind, int K, const int *p, const int *nbr, int
 
 namespace {
 
+// w < 0: the library's own split, -w work-groups per CU
 pb_status build_table(pb_batch *b, pb_batch::RunTable &tab, int kind, int w, bool applies)
 {
-    if (tab.w == w && (tab.d || w <= 0 || !applies)) return PB_OK;
+    if (tab.w == w && (tab.d || w == 0 || !applies)) return PB_OK;
     tab.w = 0;
     if (tab.d) {
         PB_HIP(hipFree(tab.d));
         tab.d = nullptr;
         tab.n = 0;
     }
-    if (w <= 0 || !applies) {
+    if (w == 0 || !applies) {
         tab.w = w;
         return PB_OK;
     }
     int cus = 0;
     pb_status st = device_cus(&cus);
     if (st != PB_OK) return st;
-    const std::vector<int4> runs = column_runs(kind, b->K, b->p.data(), b->nbr.data(), w, cus);
+    const std::vector<int4> runs = column_runs(kind, b->K, b->p.data(), b->nbr.data(), std::abs(w), cus, w < 0);
     if ((long long)runs.size() > max_units(b->K)) { set_error("column runs exceed the partial buffers"); return PB_EINVAL; }
     void *d = nullptr;
     PB_HIP(hipMalloc(&d, runs.size() * sizeof(int4)));
@@ -1289,9 +1295,29 @@ pb_status build_table(pb_batch *b, pb_batch::RunTable &tab, int kind, int w, boo
 
 pb_status runs_prepare(pb_batch *b)
 {
-    pb_status st = build_table(b, b->fv_runs, 0, b->fv_column, b->dim == 3);
+    // FV: without a tuning, runs that fill the device's three work-groups per
+    // CU once.  16^3 patches, FP64, us per step with one work-group per patch
+    // and with these runs: 8 patches 27.9 and 6.8, 64 28.7 and 11.0, 256 33.0
+    // and 28.6, 1024 87.4 and 83.3, 2048 163 and 159; 1728 patches of 8^3 50.9
+    // and 42.4; relativistic, 2048 of 16^3, 316 and 304 with the con2prim pass.
+    const bool own = b->fv_slab == 0 && b->fv_persist == 0 && b->fv_column == 0 && !b->fv_dma && !fv_small_eligible(b) &&
+                     b->pde != PB_PDE_LINSYM;
+    pb_status st = build_table(b, b->fv_runs, 0, own ? -3 : b->fv_column, b->dim == 3);
     if (st != PB_OK) return st;
-    return build_table(b, b->fd_runs, 1, b->fd_column, b->dim == 3 && b->pde == PB_PDE_EULER);
+    const bool fd = b->dim == 3 && b->pde == PB_PDE_EULER;
+    int w = b->fd_column;
+    if (fd && w == 2) {
+        // the default: runs shorter than a patch where the batch has fewer
+        // patches than resident work-groups.  A step of 16^3 patches with
+        // whole patches and with these runs: 1 patch 157 and 34 us, 64 168 and
+        // 68, 256 184 and 163, 384 257 and 218 (7 planes of start-up per run
+        // against CUs without work; runs of at least 2, 3 or 4 planes were no
+        // better for any of these).
+        int cus = 0;
+        if ((st = device_cus(&cus)) != PB_OK) return st;
+        if (b->K < 2 * cus) w = -2;
+    }
+    return build_table(b, b->fd_runs, 1, w, fd);
 }
 
 bool fv_small_eligible(const pb_batch *b)
