@@ -41,7 +41,7 @@ WsLayout ws_layout(int pde, int dim, int h, long long total_cells, int N, int st
     o += sizeof(Ctrl);
     o = align256(o);
     L.part = o;
-    // [8][units] partials, then [8][units / 256 + 1] for the second reduction stage
+    // [8][units] partials, then as many as the lines need where K is small
     const size_t part = (size_t)8 * ((size_t)max_units(K) + (size_t)max_units(K) / 256 + 1) * sizeof(double);
     // the hand-over lines take the end of the partials, beyond the 3 K values
     // that the first kernel of an FV call stores (K = 1: 136 values, 96 of
@@ -210,7 +210,7 @@ static pb_status enqueue_fv(pb_batch *b, double cfl, double dt_fixed, int n, hip
     for (int i = 0; i < n; ++i) {
         const int slot = i & 1;
         if (b->pde == PB_PDE_SRHD)
-            if ((st = launch_srhd_c2p(b, b->state[cur], slot, cfl_mode, cfl, s)) != PB_OK) return st;
+            if ((st = launch_srhd_c2p(b, b->state[cur], s)) != PB_OK) return st;
         if (span)
             arm_events(b, i == 0, i == n - 1);
         else

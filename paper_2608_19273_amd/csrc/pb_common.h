@@ -41,8 +41,7 @@ struct Ctrl {
     unsigned long long c2p_fallback;
     unsigned int c2p_maxit;
     unsigned int pad0;
-    double last_dt;
-    unsigned long long pad[19];
+    unsigned long long pad[20];
 };
 static_assert(sizeof(Ctrl) == 256, "Ctrl layout");
 
@@ -181,13 +180,14 @@ __device__ __forceinline__ void store_partial(double *__restrict__ part, const d
 // slots were no better where the work-groups read one slot while others fold
 // into the next (132 us): a slot's lines are read or folded into, not both.
 constexpr int kLamUnits = 1024;
+constexpr int kC2pUnits = 2048;   // SRHD: partials of the con2prim pass
 constexpr int kLines = 8;
 struct FvChain {
     int step;
     double cfl, dxmin;
     unsigned long long *lines;   // [3 slots][n_lines][16], direction d at d
     int n_lines;                 // a power of two, at most kLines
-    const double *part;          // step 0: the partials
+    const double *part;          // step 0 (SRHD: every step): the partials
     int n_part;
 };
 
@@ -200,34 +200,85 @@ __device__ __forceinline__ double chain_dt(const double *lam, const FvChain &c)
     return c.cfl / den;
 }
 
-// the step's dt: fixed, from the call's starting state, handed over from the
-// previous step of the call, or from the reduction kernel (SRHD).  Every
-// thread of the work-group calls it.
-template <int DIM, bool kLam>
-__device__ __forceinline__ double step_dt(const Ctrl *ctrl, int slot_in, double dt_fixed, const FvChain &c)
+// largest value of each row of the partials [DIM][n_part], n_part <= MAXN, in
+// every thread
+template <int DIM, int MAXN>
+__device__ __forceinline__ void part_max(const FvChain &c, double *lam)
 {
-    if (!kLam) return dt_fixed > 0.0 ? dt_fixed : ctrl->dt[slot_in];
+    __shared__ double red[DIM][kFvThreads / kWave];
     const int t = threadIdx.x, lane = t & (kWave - 1);
+    // all loads in flight at once: past the end the last entry again
+    double v[DIM][MAXN / kFvThreads];
+#pragma unroll
+    for (int j = 0; j < MAXN / kFvThreads; ++j) {
+        const int i = min(t + j * kFvThreads, c.n_part - 1);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) v[d][j] = c.part[d * c.n_part + i];
+    }
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) {
+#pragma unroll
+        for (int j = 0; j < MAXN / kFvThreads; ++j) lam[d] = fmax(lam[d], v[d][j]);
+        lam[d] = wave_max(lam[d]);
+        if (lane == 0) red[d][t / kWave] = lam[d];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < DIM; ++d)
+#pragma unroll
+        for (int w = 0; w < kFvThreads / kWave; ++w) lam[d] = fmax(lam[d], red[d][w]);
+}
+
+// Adds the con2prim statistics of a step (rows 3-7 of its partials [8][n_part]:
+// iterations, failures, largest iteration count, fallbacks, cells) to the
+// control block; one work-group of the launch calls it.  Sums of integers
+// held exactly in doubles: the order does not matter.
+__device__ __forceinline__ void add_c2p_stats(Ctrl *ctrl, const FvChain &c)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int r = 3 + (int)threadIdx.x / kWave; r < 8; r += kFvThreads / kWave) {
+        double v = 0.0;
+        for (int i = lane; i < c.n_part; i += kWave) {
+            const double u = c.part[r * c.n_part + i];
+            v = r == 5 ? fmax(v, u) : v + u;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const double u = __shfl_xor(v, o, kWave);
+            v = r == 5 ? fmax(v, u) : v + u;
+        }
+        if (lane != 0) continue;
+        if (r == 3) ctrl->c2p_iters += (unsigned long long)v;
+        if (r == 4) ctrl->c2p_fail += (unsigned long long)v;
+        if (r == 5) ctrl->c2p_maxit = max(ctrl->c2p_maxit, (unsigned)v);
+        if (r == 6) ctrl->c2p_fallback += (unsigned long long)v;
+        if (r == 7) ctrl->c2p_cells += (unsigned long long)v;
+    }
+}
+
+// the step's dt: fixed, from the call's starting state, handed over from the
+// previous step of the call, or (kC2p: SRHD) from the partials of the con2prim
+// pass before it, whose statistics work-group 0 also adds up.  Every thread of
+// the work-group calls it.
+template <int DIM, bool kLam, bool kC2p = false>
+__device__ __forceinline__ double step_dt(Ctrl *ctrl, int slot_in, double dt_fixed, const FvChain &c)
+{
     double lam[DIM];
 #pragma unroll
     for (int d = 0; d < DIM; ++d) lam[d] = 0.0;
+    if constexpr (kC2p) {
+        if (blockIdx.x == 0) add_c2p_stats(ctrl, c);
+        if (dt_fixed > 0.0) return dt_fixed;
+        part_max<DIM, kC2pUnits>(c, lam);
+        const double dt = chain_dt<DIM>(lam, c);
+        if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->dt[slot_in] = dt;
+        return dt;
+    }
+    if (!kLam) return dt_fixed;
     if (c.step == 0) {
-        __shared__ double red[DIM][kFvThreads / kWave];
-        for (int i = t; i < c.n_part; i += kFvThreads)
-#pragma unroll
-            for (int d = 0; d < DIM; ++d) lam[d] = fmax(lam[d], c.part[d * c.n_part + i]);
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-            lam[d] = wave_max(lam[d]);
-            if (lane == 0) red[d][t / kWave] = lam[d];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int d = 0; d < DIM; ++d)
-#pragma unroll
-            for (int w = 0; w < kFvThreads / kWave; ++w) lam[d] = fmax(lam[d], red[d][w]);
+        part_max<DIM, kLamUnits>(c, lam);
     } else {
         static_assert(kLines == 8, "one line per lane of eight");
+        const int lane = threadIdx.x & (kWave - 1);
         const unsigned long long *l = c.lines + 16 * ((c.step + 2) % 3 * c.n_lines + (lane & (c.n_lines - 1)));
 #pragma unroll
         for (int d = 0; d < DIM; ++d) lam[d] = max8(__longlong_as_double((long long)l[d]));
@@ -436,8 +487,11 @@ FvChain fv_chain(const pb_batch *b, int step, double cfl);
 pb_status device_cus(int *out);
 pb_status launch_fv_step(pb_batch *b, const void *qin, void *qout, int slot_in, int step, double dt_fixed,
                          double cfl, hipStream_t s);
-pb_status launch_srhd_c2p(pb_batch *b, const void *q, int slot_out, bool want_dt, double cfl,
-                          hipStream_t s);
+// con2prim pass of state q: pressures, and partials (largest speeds,
+// statistics) that the FV step after it reduces
+pb_status launch_srhd_c2p(pb_batch *b, const void *q, hipStream_t s);
+// the number of those partials per row
+int c2p_units(const pb_batch *b);
 // one stage of the linear system's step: `out` from Q0 and the stage input y
 // (stage 0: Q0 itself); the last RK4 stage also reads the earlier stages'
 // values y1 and y2, and out may be y1
@@ -477,6 +531,4 @@ double fd_dt(const pb_batch *b, double cfl, double dt_fixed);
 // uploads the FD work list and B_d (library-owned; done once, before any capture)
 pb_status fd_prepare(pb_batch *b);
 pb_status launch_ctrl_init(pb_batch *b, hipStream_t s);
-pb_status launch_dt_reduce(pb_batch *b, const double *part, int n_units, int dim, int slot, double cfl, bool want_dt,
-                           bool want_stats, hipStream_t s);
 }  // namespace pb

@@ -120,7 +120,7 @@ __device__ __forceinline__ void load5u_nt(const double *__restrict__ base, unsig
 // a stage's dt: fixed; from the hand-over in a step's first stage, which
 // records it; from that record in the stages after it
 template <int S>
-__device__ __forceinline__ double stage_dt(const Ctrl *ctrl, int slot, double dt_fixed, const FvChain &chain)
+__device__ __forceinline__ double stage_dt(Ctrl *ctrl, int slot, double dt_fixed, const FvChain &chain)
 {
     if (dt_fixed > 0.0) return dt_fixed;
     if (S == 0 || S == 4) return step_dt<3, true>(ctrl, slot, dt_fixed, chain);

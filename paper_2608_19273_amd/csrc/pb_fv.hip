@@ -28,9 +28,6 @@
 
 namespace pb {
 
-constexpr int kReduceSpan = 256;    // units per work-group of the first reduction stage
-constexpr int kReduceOne = 8192;    // up to this many units the single-work-group reduction runs alone
-
 namespace {
 
 template <class Ph, typename T>
@@ -149,7 +146,7 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
 
     const int t = threadIdx.x;
     const int unit = plan.remap ? xcd_remap(blockIdx.x, plan.n_units) : (int)blockIdx.x;
-    const double dt = step_dt<DIM, kLam>(ctrl, slot_in, dt_fixed, chain);
+    const double dt = step_dt<DIM, kLam, (Ph::E > 0)>(ctrl, slot_in, dt_fixed, chain);
     double lm[3] = {0.0, 0.0, 0.0};
     bool bad = false;
     int parity = 0;   // LDS buffer of the next plane (alternates over every plane the work-group marches)
@@ -512,7 +509,7 @@ __global__ __launch_bounds__(kFvThreads, 2) void fv_step_dma_kernel(
     const bool work = z0 < p;
     const bool active = work && t < pp;
     const int x = active ? t % p : 0, y = active ? t / p : 0;
-    const double dt = step_dt<3, kLam>(ctrl, slot_in, dt_fixed, chain);
+    const double dt = step_dt<3, kLam, (Ph::E > 0)>(ctrl, slot_in, dt_fixed, chain);
     const double hr_ = 0.5 * dt * P.inv_dx;
     // LDS slots of the cell and its four in-plane neighbours (halo strips
     // follow the p x p interior: -x, +x, -y, +y, p cells each)
@@ -719,7 +716,7 @@ __global__ __launch_bounds__(kFvThreads, kSelf ? 4 : 3) void fv_small_kernel(
     const int P2 = p * p, P3 = P2 * p, HP = 6 * P2, NC = G * P3;
     const int g = t / P3, l = t - g * P3;
     const int x = l % p, y = (l / p) % p, z = l / P2;
-    const double dt = step_dt<3, kLam>(ctrl, slot_in, dt_fixed, chain);
+    const double dt = step_dt<3, kLam, (Ph::E > 0)>(ctrl, slot_in, dt_fixed, chain);
     const int grid = (int)gridDim.x, first = xcd_remap(blockIdx.x, grid);
 
     // LDS slots of the six face neighbours (threads beyond the group's cells: slot 0)
@@ -898,101 +895,6 @@ __global__ __launch_bounds__(kFvThreads) void fv_lambda_kernel(const T *__restri
     }
 }
 
-// dt from the partial maxima: Lambda_d = max over units, then
-// dt = cfl / sum_d (Lambda_d / dx_min), written to ctrl->dt[slot].  With
-// stats, rows 3..7 of the partials (con2prim iterations, failures, largest
-// iteration count, fallbacks, cells) are folded into the control block.
-// One work-group; every thread issues the loads of all rows of a unit
-// together (one memory round trip per unit, not one per row).  Maxima are
-// exact and the sums are of integers held exactly in doubles, so the result
-// does not depend on the order.
-__global__ __launch_bounds__(1024) void dt_reduce_kernel(const double *__restrict__ part, int n_units, int dim,
-                                                         Ctrl *__restrict__ ctrl, int slot, double cfl,
-                                                         double dxmin, int want_dt, int want_stats)
-{
-    __shared__ double red[8][1024 / kWave];
-    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
-    const int rows = want_stats ? 8 : dim;
-    // row r is used when r < dim, or r >= 3 with stats; max for rows 0-2 and 5
-    double m[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) m[r] = 0.0;
-    for (int i = t; i < n_units; i += blockDim.x) {
-        double v[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v[r] = (r < rows && !(r >= dim && r < 3)) ? part[(long long)r * n_units + i] : 0.0;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) m[r] = (r < 3 || r == 5) ? fmax(m[r], v[r]) : m[r] + v[r];
-    }
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const bool mx = r < 3 || r == 5;
-        double a = m[r];
-        for (int o = 32; o > 0; o >>= 1) {
-            const double u = __shfl_xor(a, o, kWave);
-            a = mx ? fmax(a, u) : a + u;
-        }
-        if (lane == 0) red[r][w] = a;
-    }
-    __syncthreads();
-    if (t == 0) {
-        double tot[8];
-        for (int r = 0; r < rows; ++r) {
-            if (r >= dim && r < 3) continue;
-            const bool mx = r < 3 || r == 5;
-            double a = red[r][0];
-            for (int i = 1; i < (int)(blockDim.x / kWave); ++i) a = mx ? fmax(a, red[r][i]) : a + red[r][i];
-            tot[r] = a;
-        }
-        if (want_dt) {
-            double den = 0.0;
-            for (int d = 0; d < dim; ++d) den += tot[d] / dxmin;
-            const double dt = cfl / den;
-            ctrl->dt[slot] = dt;
-            ctrl->last_dt = dt;
-        }
-        if (want_stats) {
-            ctrl->c2p_iters += (unsigned long long)tot[3];
-            ctrl->c2p_fail += (unsigned long long)tot[4];
-            if ((unsigned)tot[5] > ctrl->c2p_maxit) ctrl->c2p_maxit = (unsigned)tot[5];
-            ctrl->c2p_fallback += (unsigned long long)tot[6];
-            ctrl->c2p_cells += (unsigned long long)tot[7];
-        }
-    }
-}
-
-// first stage of the partial reduction: work-group g folds units
-// [g*kReduceSpan, (g+1)*kReduceSpan) of every row (max for rows 0-2 and 5,
-// sum otherwise) into out[r * n_out + g]
-__global__ __launch_bounds__(256) void partial_reduce_kernel(const double *__restrict__ part, int n_units, int rows,
-                                                             int dim, double *__restrict__ out, int n_out)
-{
-    __shared__ double red[256 / kWave];
-    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
-    const int u0 = blockIdx.x * kReduceSpan, u1 = min(n_units, u0 + kReduceSpan);
-    for (int r = 0; r < rows; ++r) {
-        if (r >= dim && r < 3) continue;
-        const bool mx = r < 3 || r == 5;
-        double m = 0.0;
-        for (int i = u0 + t; i < u1; i += 256) {
-            const double v = part[(long long)r * n_units + i];
-            m = mx ? fmax(m, v) : m + v;
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            const double u = __shfl_xor(m, o, kWave);
-            m = mx ? fmax(m, u) : m + u;
-        }
-        if (lane == 0) red[w] = m;
-        __syncthreads();
-        if (t == 0) {
-            double a = red[0];
-            for (int i = 1; i < 256 / kWave; ++i) a = mx ? fmax(a, red[i]) : a + red[i];
-            out[(long long)r * n_out + blockIdx.x] = a;
-        }
-        __syncthreads();
-    }
-}
-
 __global__ void ctrl_init_kernel(Ctrl *ctrl)
 {
     // zero the whole control block with vector stores (no memset node, so
@@ -1024,7 +926,8 @@ FvChain fv_chain(const pb_batch *b, int step, double cfl)
 {
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
     return FvChain{step, cfl, b->dxmin, reinterpret_cast<unsigned long long *>(b->ws + L.lines), L.n_lines,
-                   reinterpret_cast<const double *>(b->ws + L.part), std::min(b->K, kLamUnits)};
+                   reinterpret_cast<const double *>(b->ws + L.part),
+                   b->pde == PB_PDE_SRHD ? c2p_units(b) : std::min(b->K, kLamUnits)};
 }
 
 namespace {
@@ -1359,27 +1262,6 @@ pb_status launch_fv_lambda(pb_batch *b, const void *q, hipStream_t s)
             return launch_lambda_typed<Ph, DIM, T>(b, ph, q, s);
         }
     });
-}
-
-pb_status launch_dt_reduce(pb_batch *b, const double *part, int n_units, int dim, int slot, double cfl, bool want_dt,
-                           bool want_stats, hipStream_t s)
-{
-    if (!want_dt && !want_stats) return PB_OK;
-    const int rows = want_stats ? 8 : dim;
-    if (n_units > kReduceOne) {
-        // first stage: one work-group per kReduceSpan units, partials of the
-        // partials into the tail of the partial buffer
-        const int g = (n_units + kReduceSpan - 1) / kReduceSpan;
-        double *part2 = const_cast<double *>(part) + (size_t)8 * max_units(b->K);
-        hipLaunchKernelGGL(partial_reduce_kernel, dim3(g), dim3(256), 0, s, part, n_units, rows, dim, part2, g);
-        PB_HIP(hipGetLastError());
-        part = part2;
-        n_units = g;
-    }
-    hipLaunchKernelGGL(dt_reduce_kernel, dim3(1), dim3(1024), 0, s, part, n_units, dim, reinterpret_cast<Ctrl *>(b->ws),
-                       slot, cfl, b->dxmin, want_dt ? 1 : 0, want_stats ? 1 : 0);
-    PB_HIP(hipGetLastError());
-    return PB_OK;
 }
 
 pb_status launch_ctrl_init(pb_batch *b, hipStream_t s)

@@ -1,7 +1,7 @@
 // pb_srhd.hip -- the per-cell conservative-to-primitive pass of the SRHD
 // finite-volume step, and the standalone con2prim entry point.
 //
-// The SRHD step is two launches (plus the small dt reduction):
+// The SRHD step is two launches:
 //   1. this pass: one lane per cell recovers the pressure by the bracketed
 //      FP64 Newton iteration (pb_c2p.h), seeded by the plain guess, the
 //      previous step's pressure (warm) or the MLP (learned, evaluated in the
@@ -9,7 +9,10 @@
 //      workspace and per-work-group partials: largest speeds of Q^n (for dt),
 //      Newton iterations, failures, fallbacks;
 //   2. the fused Rusanov kernel (pb_fv.hip) with the SRHD functor, which
-//      reads p of each cell and its face neighbours.
+//      reads p of each cell and its face neighbours, forms dt from the
+//      partials in every work-group and adds the statistics up in one.  (A
+//      reduction launch of its own between the two took 21 us of a 336 us
+//      step of 2048 patches of 16^3, and 4096 partials per row to read.)
 // Failures never stop the step; they are counted and reported by
 // pb_batch_stats (a failed cell carries the last Newton iterate).
 #include <algorithm>
@@ -116,9 +119,8 @@ __device__ __forceinline__ C2pOut solve_cell_i(const C2pIn &in, double gam, doub
     return o;
 }
 
-// Chunks of 256 cells a work-group of the con2prim passes walks: the
-// learned pass copies the network to LDS once per work-group, and every
-// pass reduces its statistics once per work-group.
+// Chunks of 256 cells a work-group of the standalone learned con2prim walks
+// (it copies the network to LDS and reduces its statistics once for them).
 constexpr int kLearnChunks = 8;
 
 // the same LDS object behind an offset the compiler cannot see through: keeps
@@ -154,17 +156,96 @@ __device__ __forceinline__ const MlpPack &mlp_lane_setup(const MlpPack *__restri
     return sp;
 }
 
-// The con2prim pass of one work-group: kLearnChunks chunks of 256 cells of
-// its patch, the next chunk's state (and, for the warm start, the previous
-// pressure) loaded while the current one is solved, one statistics
-// reduction for all of them.  GUESS: PB_GUESS_PLAIN (Newton from p_hi),
-// PB_GUESS_WARM (from the previous pressure in pres), PB_GUESS_LEARNED (from
-// the network, evaluated here on the matrix cores; `pack` is the inference
-// blob, copied to LDS once).  A guessed start that does not converge is
-// redone from p_hi.  The speeds of the recovered state feed the next dt.
-template <int GUESS>
+// How a con2prim pass deals the cells to its work-groups: unit u takes the
+// chunks u, u + n_units, ... of 256 cells and ends with one entry per row of
+// the partials.  Patches of one size: the chunks run through all cells of the
+// batch, so lanes stay busy whatever p is.  Mixed sizes: chunks of one patch
+// each, `chunks` per patch (those beyond a patch's cells are empty), and an
+// n_units that shares no factor with `chunks`, so that every unit meets short
+// and long patches alike.
+// At most kC2pUnits units, since every work-group of the FV step reads all
+// partials: 2048 of them (2048 patches of 16^3) take 127 us here and 188 us
+// in the FV step, 1024 take 133 us (fewer than the six work-groups per CU
+// that the registers allow, and no second round to fill the gaps of waves
+// whose cells converge sooner), 4096 take 129 us here but 213 us there.
+struct C2pPlan {
+    int n_units, chunks;   // chunks: per patch (mixed sizes), or 0
+    int C;                 // cells of a patch (one size)
+    int dk, dr;            // a unit's stride in whole patches, and in cells (one size) or chunks
+    float iC;              // 1 / C
+    long long total;       // one size: cells; mixed: chunks
+};
+
+// a chunk: the first cell of its (first) patch, the cells of a patch, and the
+// lane's element of unknown 0 and its cell, both from there
+struct C2pCell {
+    long long off;
+    int C;
+    unsigned o, i;
+    bool on;
+};
+
+// the chunks in the order in which a work-group visits them (everything but
+// the lane's own offsets is the same for the whole work-group); past the last
+// chunk, and for lanes without a cell, the batch's or the patch's first cell,
+// so that every lane can always load
+template <bool kOneSize>
+struct C2pWalk {
+    const PatchDev *patches;
+    C2pPlan plan;
+    long long g;   // next chunk
+    int k, r;      // its patch, and the cell of its first lane (one size) or its number in the patch
+
+    __device__ __forceinline__ C2pWalk(const PatchDev *pt, const C2pPlan &pl)
+        : patches(pt), plan(pl), g(blockIdx.x), k(0), r(0)
+    {
+        const int c = blockIdx.x * (kOneSize ? kC2pThreads : 1), d = kOneSize ? plan.C : plan.chunks;
+        k = c / d;
+        r = c - k * d;
+    }
+    __device__ __forceinline__ bool more() const { return kOneSize ? g * kC2pThreads < plan.total : g < plan.total; }
+    __device__ __forceinline__ C2pCell next()
+    {
+        C2pCell c;
+        const int t = threadIdx.x;
+        const bool any = more();
+        if (kOneSize) {
+            // patches passed from the chunk's first cell to the lane's: the
+            // quotient of two integers below 2^13, exact with the half
+            const int x = r + t, dk = (int)(((float)x + 0.5f) * plan.iC);
+            c.off = any ? (long long)k * plan.C : 0;
+            c.C = plan.C;
+            c.on = t < plan.total - g * kC2pThreads;
+            c.i = x;
+            c.o = x + dk * 4 * plan.C;
+        } else {
+            const PatchDev &P = patches[any ? k : 0];
+            c.off = P.off;
+            c.C = P.p * P.p * P.p;
+            c.i = c.o = r * kC2pThreads + t;
+            c.on = any && (int)c.i < c.C;
+        }
+        if (!c.on) c.i = c.o = 0;
+        const int d = kOneSize ? plan.C : plan.chunks;
+        k += plan.dk;
+        r += plan.dr;
+        if (r >= d) { r -= d; ++k; }
+        g += plan.n_units;
+        return c;
+    }
+};
+
+// The con2prim pass of one work-group (see C2pPlan), the next chunk's state
+// (and, for the warm start, the previous pressure) loaded while the current
+// one is solved, one statistics reduction at the end.  GUESS: PB_GUESS_PLAIN
+// (Newton from p_hi), PB_GUESS_WARM (from the previous pressure in pres),
+// PB_GUESS_LEARNED (from the network, evaluated here on the matrix cores;
+// `pack` is the inference blob, copied to LDS once).  A guessed start that
+// does not converge is redone from p_hi.  The speeds of the recovered state
+// give the step's dt.
+template <int GUESS, bool kOneSize>
 __device__ __forceinline__ void c2p_pass(const double *__restrict__ q, double *__restrict__ pres,
-                                         const PatchDev *__restrict__ patches, int gchunks, int n_units,
+                                         const PatchDev *__restrict__ patches, const C2pPlan &plan,
                                          double *__restrict__ part, double gam, double tol, int maxit,
                                          const MlpPack *__restrict__ pack)
 {
@@ -172,35 +253,30 @@ __device__ __forceinline__ void c2p_pass(const double *__restrict__ q, double *_
     MlpLane L;
     const MlpPack *sp = nullptr;
     if constexpr (kLearned) sp = &mlp_lane_setup(pack, L);
-    const int unit = blockIdx.x;
-    const int k = unit / gchunks, gc = unit - k * gchunks;
-    const PatchDev P = patches[k];
-    const long long C = (long long)P.p * P.p * P.p;
-    const double *base = q + P.off * 5;
-    double *pb = pres + P.off;
     CellAcc acc;
-    const long long c0 = (long long)gc * kLearnChunks * kC2pThreads + threadIdx.x;
     double nx[5] = {1.0, 0.0, 0.0, 0.0, 1.0}, npv = 0.0;
-    if (c0 < C) {
+    C2pWalk<kOneSize> walk(patches, plan);
+    auto load = [&](const C2pCell &c) {
+        const double *base = q + c.off * 5;
 #pragma unroll
-        for (int v = 0; v < 5; ++v) nx[v] = base[(long long)v * C + c0];
-        if (kWarm) npv = pb[c0];
-    }
+        for (int v = 0; v < 5; ++v) nx[v] = (base + (long long)v * c.C)[c.o];
+        if (kWarm) npv = (pres + c.off)[c.i];
+    };
+    bool any = walk.more();
+    C2pCell cell = walk.next();
+    load(cell);
 #pragma unroll 1
-    for (int gi = 0; gi < kLearnChunks; ++gi) {
-        const long long c = c0 + (long long)gi * kC2pThreads;
-        if (c - threadIdx.x >= C) break;   // the same for the whole work-group
-        const bool active = c < C;
+    while (any) {
+        const bool active = cell.on;
         double qv[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) qv[v] = nx[v];
         const double pprev = npv;
-        const long long cn = c + kC2pThreads;
-        if (gi + 1 < kLearnChunks && cn < C) {
-#pragma unroll
-            for (int v = 0; v < 5; ++v) nx[v] = base[(long long)v * C + cn];
-            if (kWarm) npv = pb[cn];
-        }
+        double *pb = pres + cell.off;
+        const unsigned pi = cell.i;
+        any = walk.more();
+        cell = walk.next();
+        load(cell);
         const C2pIn in = c2p_setup(qv[0], qv[1], qv[2], qv[3], qv[4], gam);
         double p0 = in.hi;
         if constexpr (kLearned) p0 = mlp_guess(lds_fresh(*sp), L.xm, L.xi, L.ym, L.ys, in);   // whole wave
@@ -209,7 +285,7 @@ __device__ __forceinline__ void c2p_pass(const double *__restrict__ q, double *_
             C2pOut o;
             if constexpr (GUESS == PB_GUESS_PLAIN) o = c2p_solve(in, gam, tol, maxit, p0);
             else o = solve_cell_i(in, gam, tol, maxit, p0, acc.fallbacks);
-            pb[c] = o.p;
+            pb[pi] = o.p;
             const Srhd ph{gam};
             double a[Srhd::A], e[1] = {o.p};
             ph.aux_fast(qv, e, a);
@@ -223,24 +299,25 @@ __device__ __forceinline__ void c2p_pass(const double *__restrict__ q, double *_
     if (threadIdx.x == 0) {
         const double v[8] = {s.lam[0], s.lam[1], s.lam[2], s.iters, s.fails, s.maxit, s.fallbacks, s.cells};
 #pragma unroll
-        for (int r = 0; r < 8; ++r) part[(long long)r * n_units + unit] = v[r];
+        for (int r = 0; r < 8; ++r) part[r * plan.n_units + blockIdx.x] = v[r];
     }
 }
 
 // plain (GUESS 0) or warm (GUESS 2) start
-template <int GUESS>
+template <int GUESS, bool kOneSize>
 __global__ __launch_bounds__(kC2pThreads) void srhd_c2p_kernel(
-    const double *__restrict__ q, double *__restrict__ pres, const PatchDev *__restrict__ patches, int gchunks,
-    int n_units, double *__restrict__ part, double gam, double tol, int maxit)
+    const double *__restrict__ q, double *__restrict__ pres, const PatchDev *__restrict__ patches, C2pPlan plan,
+    double *__restrict__ part, double gam, double tol, int maxit)
 {
-    c2p_pass<GUESS>(q, pres, patches, gchunks, n_units, part, gam, tol, maxit, nullptr);
+    c2p_pass<GUESS, kOneSize>(q, pres, patches, plan, part, gam, tol, maxit, nullptr);
 }
 
+template <bool kOneSize>
 __global__ __launch_bounds__(kC2pThreads, 4) void srhd_c2p_learned_kernel(
-    const double *__restrict__ q, double *__restrict__ pres, const PatchDev *__restrict__ patches, int gchunks,
-    int n_units, double *__restrict__ part, double gam, double tol, int maxit, const MlpPack *__restrict__ pack)
+    const double *__restrict__ q, double *__restrict__ pres, const PatchDev *__restrict__ patches, C2pPlan plan,
+    double *__restrict__ part, double gam, double tol, int maxit, const MlpPack *__restrict__ pack)
 {
-    c2p_pass<PB_GUESS_LEARNED>(q, pres, patches, gchunks, n_units, part, gam, tol, maxit, pack);
+    c2p_pass<PB_GUESS_LEARNED, kOneSize>(q, pres, patches, plan, part, gam, tol, maxit, pack);
 }
 
 // standalone con2prim, one cell of SoA arrays: primitives out
@@ -332,40 +409,67 @@ __global__ __launch_bounds__(kC2pThreads, 4) void con2prim_learned_kernel(
 
 }  // namespace
 
-pb_status launch_srhd_c2p(pb_batch *b, const void *q, int slot_out, bool want_dt, double cfl, hipStream_t s)
+namespace {
+
+C2pPlan c2p_plan(const pb_batch *b)
+{
+    C2pPlan pl{};
+    const int cmax = b->pmax * b->pmax * b->pmax;
+    if (b->uniform_p) {
+        pl.C = cmax;
+        pl.iC = 1.0f / (float)cmax;
+        pl.total = b->total_cells;
+        pl.n_units = (int)std::min<long long>((pl.total + kC2pThreads - 1) / kC2pThreads, kC2pUnits);
+        pl.dk = pl.n_units * kC2pThreads / cmax;
+        pl.dr = pl.n_units * kC2pThreads % cmax;
+    } else {
+        pl.chunks = (cmax + kC2pThreads - 1) / kC2pThreads;   // at most 16
+        pl.total = (long long)b->K * pl.chunks;
+        pl.n_units = (int)std::min<long long>(pl.total, kC2pUnits - 9);   // 2039, a prime
+        pl.dk = pl.n_units / pl.chunks;
+        pl.dr = pl.n_units % pl.chunks;
+    }
+    return pl;
+}
+
+}  // namespace
+
+int c2p_units(const pb_batch *b) { return c2p_plan(b).n_units; }
+
+pb_status launch_srhd_c2p(pb_batch *b, const void *q, hipStream_t s)
 {
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
     double *pres = reinterpret_cast<double *>(b->ws + L.pres);
     double *part = reinterpret_cast<double *>(b->ws + L.part);
-    const long long cmax = (long long)b->pmax * b->pmax * b->pmax;
-    const int chunks = (int)((cmax + kC2pThreads - 1) / kC2pThreads);
     const double gam = b->params[0], tol = b->params[1];
     const int maxit = (int)b->params[2];
     int guess = b->guess;
     if (guess == PB_GUESS_WARM && !b->pres_valid) guess = PB_GUESS_PLAIN;
     const double *qd = static_cast<const double *>(q);
-    const int gchunks = (chunks + kLearnChunks - 1) / kLearnChunks;
-    const int n_units = b->K * gchunks;
+    const C2pPlan plan = c2p_plan(b);
+    auto go = [&](auto kern, auto... more) {
+        hipLaunchKernelGGL(kern, dim3(plan.n_units), dim3(kC2pThreads), 0, s, qd, pres, b->d_patches, plan, part, gam,
+                           tol, maxit, more...);
+    };
+    const bool one = plan.chunks == 0;
     switch (guess) {
     case PB_GUESS_PLAIN:
-        hipLaunchKernelGGL(srhd_c2p_kernel<PB_GUESS_PLAIN>, dim3(n_units), dim3(kC2pThreads), 0, s, qd, pres,
-                           b->d_patches, gchunks, n_units, part, gam, tol, maxit);
+        one ? go(srhd_c2p_kernel<PB_GUESS_PLAIN, true>) : go(srhd_c2p_kernel<PB_GUESS_PLAIN, false>);
         break;
     case PB_GUESS_LEARNED: {
         MlpDev md{};
         pb_status st = mlp_device_view(b->mlp, &md);
         if (st != PB_OK) return st;
-        hipLaunchKernelGGL(srhd_c2p_learned_kernel, dim3(n_units), dim3(kC2pThreads), 0, s, qd, pres, b->d_patches,
-                           gchunks, n_units, part, gam, tol, maxit, md.pack);
+        one ? go(srhd_c2p_learned_kernel<true>, (const MlpPack *)md.pack)
+            : go(srhd_c2p_learned_kernel<false>, (const MlpPack *)md.pack);
         break;
     }
     default:
-        hipLaunchKernelGGL(srhd_c2p_kernel<PB_GUESS_WARM>, dim3(n_units), dim3(kC2pThreads), 0, s, qd, pres,
-                           b->d_patches, gchunks, n_units, part, gam, tol, maxit);
+        one ? go(srhd_c2p_kernel<PB_GUESS_WARM, true>) : go(srhd_c2p_kernel<PB_GUESS_WARM, false>);
     }
     PB_HIP(hipGetLastError());
     b->pres_valid = true;
-    return launch_dt_reduce(b, part, n_units, 3, slot_out, cfl, want_dt, true, s);
+    return PB_OK;
 }
 
 }  // namespace pb

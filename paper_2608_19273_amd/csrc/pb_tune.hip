@@ -222,7 +222,7 @@ pb_status pb_autotune(pb_batch *b, int32_t kind, double cfl, double dt_fixed, do
     pb_status st = PB_OK;
     if (kind == 0) {
         if (b->pde == PB_PDE_SRHD)
-            st = launch_srhd_c2p(b, b->state[b->cur], 0, cfl_mode, cfl, s);
+            st = launch_srhd_c2p(b, b->state[b->cur], s);
         else if (cfl_mode)
             st = launch_fv_lambda(b, b->state[b->cur], s);
     } else if (b->pde == PB_PDE_EULER && cfl_mode) {
