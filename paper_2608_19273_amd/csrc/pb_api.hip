@@ -48,6 +48,10 @@ WsLayout ws_layout(int pde, int dim, int h, long long total_cells, int N, int st
     // them in lines; K = 4: 520 and 384)
     L.n_lines = K >= 4 ? kLines : 2;
     L.lines = (o + part - (size_t)3 * L.n_lines * 128) / 128 * 128;
+    // the bits behind the partials that are in use (SRHD: 8 rows of at most
+    // kC2pUnits, and no lines; K = 1: 8 of the 64 bytes left)
+    L.seen = o + sizeof(double) * (pde == PB_PDE_SRHD ? 8 * (size_t)std::min<long long>(max_units(K), kC2pUnits)
+                                                      : 3 * (size_t)std::min(K, kLamUnits));
     o = align256(o + part);
     if (pde == PB_PDE_SRHD) {
         L.pres = o;

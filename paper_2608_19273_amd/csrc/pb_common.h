@@ -189,7 +189,21 @@ struct FvChain {
     int n_lines;                 // a power of two, at most kLines
     const double *part;          // step 0 (SRHD: every step): the partials
     int n_part;
+    // one bit per patch: counted as not finite in this step, where the
+    // library's own split deals a patch to several work-groups and counts by
+    // patches (else null: the work-groups are counted).  The other set, the
+    // next step's, is cleared.
+    unsigned *seen, *seen_next;
+    int n_seen;                  // words of a set
 };
+
+// counts patch k once per step if a lane of the wave saw a NaN or infinity
+__device__ __forceinline__ void count_patch(Ctrl *ctrl, const FvChain &c, int k, bool bad)
+{
+    if (__ballot(bad) == 0 || (threadIdx.x & (kWave - 1)) != 0) return;
+    const unsigned bit = 1u << (k & 31);
+    if (!(atomicOr(&c.seen[k >> 5], bit) & bit)) atomicAdd(&ctrl->nonfinite, 1ull);
+}
 
 template <int DIM>
 __device__ __forceinline__ double chain_dt(const double *lam, const FvChain &c)
@@ -311,7 +325,7 @@ __device__ __forceinline__ double rk_base(double q0, double y1, double y2, doubl
 }
 
 // End of a step's work-group: counts it in ctrl->nonfinite if a lane saw a
-// NaN or infinity, folds its cells' largest speeds into the hand-over and
+// NaN or infinity (bad: not already counted by patches), folds its cells' largest speeds into the hand-over and
 // records the step's dt for the host (see FvChain).  The exchange between the
 // lanes runs on DPP moves and the one barrier waits for LDS only, so that the
 // work-group's last stores drain after it has ended its own work.
@@ -339,6 +353,8 @@ __device__ __forceinline__ void finish_step(Ctrl *ctrl, int slot_in, double dt, 
         if (b) atomicAdd(&ctrl->nonfinite, 1ull);
         if (kLam && blockIdx.x == 0) ctrl->dt[slot_in] = dt;
     }
+    if (blockIdx.x == 0)
+        for (int i = t; i < c.n_seen; i += kFvThreads) c.seen_next[i] = 0u;
     if (kLam && t < DIM) {
         double m = red[t][0];
         for (int i = 1; i < W; ++i) m = fmax(m, red[t][i]);
@@ -394,6 +410,7 @@ struct pb_batch {
     int fd_column = 2;    // Euler FD: likewise (runs of whole patches at least); 0 = one work-group per patch
     // column-run tables (int4: patch, first plane, planes, 0; one per unit)
     // of the FV and the Euler FD plane kernels, and the w each was built for
+    // (w < 0: the library's own split, fitted to the device)
     struct RunTable {
         void *d = nullptr;
         int n = 0, w = 0;
@@ -444,6 +461,7 @@ struct WsLayout {
     size_t part = 0;       // per-unit partials [8][units]: speeds (3), con2prim stats (5)
     size_t lines = 0;      // FV hand-over lines (FvChain), in the tail of the partials: no step uses both
     int n_lines = 0;
+    size_t seen = 0;       // FvChain::seen: two sets of (K + 31) / 32 words, between the partials in use and the lines
     size_t pres = 0;       // SRHD: pressure per cell (double)
     size_t yA = 0, yB = 0; // FD: stage buffers
     size_t total = 0;
@@ -457,6 +475,7 @@ inline bool fd_buffers(int pde, int dim, int h)
 WsLayout ws_layout(int pde, int dim, int h, long long total_cells, int N, int storage, int K);
 // largest number of work units any launch uses (partials are sized for it)
 inline long long max_units(int K) { return (long long)K * kFvPmax; }
+inline int seen_words(int K) { return (K + 31) / 32; }
 
 // launches a step's main kernel (the FV step, an FD stage) with its arguments
 // converted to the kernel's parameter types; when the batch is profiling, the
@@ -482,7 +501,7 @@ inline void launch_main(const pb_batch *b, void (*kern)(P...), dim3 grid, dim3 b
 // largest speeds of state q: partials for the first step of a call
 pb_status launch_fv_lambda(pb_batch *b, const void *q, hipStream_t s);
 // the hand-over of the batch for step `step` of a call
-FvChain fv_chain(const pb_batch *b, int step, double cfl);
+FvChain fv_chain(const pb_batch *b, int step, double cfl, bool by_patch);
 // compute units of the current device
 pb_status device_cus(int *out);
 pb_status launch_fv_step(pb_batch *b, const void *qin, void *qout, int slot_in, int step, double dt_fixed,
@@ -531,4 +550,6 @@ double fd_dt(const pb_batch *b, double cfl, double dt_fixed);
 // uploads the FD work list and B_d (library-owned; done once, before any capture)
 pb_status fd_prepare(pb_batch *b);
 pb_status launch_ctrl_init(pb_batch *b, hipStream_t s);
+// clears both sets of FvChain::seen (after steps that did not alternate the state buffers)
+pb_status launch_seen_init(pb_batch *b, hipStream_t s);
 }  // namespace pb

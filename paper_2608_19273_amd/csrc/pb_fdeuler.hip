@@ -412,6 +412,11 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
             // block moves up one patch (the window and the loads in flight
             // already come from it)
             z = 0;
+            if (kFinal && chain.seen) {
+                count_patch(ctrl, chain, kc, bad);
+                bad = false;
+                kc = kn;
+            }
             const long long off = patches[kn].off;
             ylo = yo;
             yo = yhi;
@@ -444,6 +449,10 @@ __global__ __launch_bounds__(kFvThreads, 2) void fd_euler_stage_kernel(
         if (++i == n) break;
         plane(std::integral_constant<int, 6>());
         ++i;
+    }
+    if (kFinal && chain.seen) {
+        count_patch(ctrl, chain, kc, bad);
+        bad = false;
     }
     if (kFinal) finish_step<3, true>(ctrl, slot, dt, lm, bad, chain);
     if (S == 0 && blockIdx.x == 0 && t == 0) ctrl->dt[slot] = dt;
@@ -825,7 +834,7 @@ pb_status launch_fd_euler_stage(pb_batch *b, int stage, int rk_stages, const voi
     const int4 *runs = (G == 0 && b->fd_column > 0 && b->fd_runs.d) ? static_cast<const int4 *>(b->fd_runs.d) : nullptr;
     const int n_units = G > 0 ? (b->K + G - 1) / G : runs ? b->fd_runs.n : b->K * n_slabs;
     Ctrl *ctrl = reinterpret_cast<Ctrl *>(b->ws);
-    const FvChain chain = fv_chain(b, step, cfl);
+    const FvChain chain = fv_chain(b, step, cfl, runs && b->fd_runs.w < 0);
     const int slot = step & 1;
     const int S = rk_stages == 1 ? 4 : stage;
     const double *yi = static_cast<const double *>(y), *q0i = static_cast<const double *>(q0);
@@ -862,7 +871,7 @@ pb_status launch_fd_euler_self(pb_batch *b, int rk_stages, const void *q0, void 
     const double *q = static_cast<const double *>(q0);
     double *o = static_cast<double *>(out);
     Ctrl *ctrl = reinterpret_cast<Ctrl *>(b->ws);
-    const FvChain chain = fv_chain(b, step, cfl);
+    const FvChain chain = fv_chain(b, step, cfl, false);
     auto go = [&](auto kern) {
         launch_main(b, kern, dim3(nwg), dim3(kFvThreads), lds, s, q, o, b->d_patches, b->K, p, G, n_groups, ctrl, chain,
                     step & 1, dt_fixed, b->params[0], sigma);

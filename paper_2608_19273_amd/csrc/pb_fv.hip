@@ -178,6 +178,7 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
     }
     const long long cxy = (long long)y * p + x;
     const long long pp = (long long)p * p;
+    int kc = k;
     // the current patch and its +z neighbour (the run's next patch): cell
     // offsets of the patch and of the wave's halo-side neighbour (lanes
     // without a halo cell load cell 0 of that neighbour and drop it)
@@ -346,6 +347,11 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
     // (already the source of the loads issued for its first planes)
     auto advance = [&](int i) {
         if (DIM == 3 && ++zl == p && i + 1 < n) {
+            if (chain.seen) {
+                count_patch(ctrl, chain, kc, bad);
+                bad = false;
+                kc = kn;
+            }
             zl = 0;
             offc = offn;
             hoffc = hoffn;
@@ -364,6 +370,10 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
         advance(i + 1);
     }
     if (i < n) plane(i, rnA, hrA, cA, cB);
+    if (DIM == 3 && chain.seen) {
+        count_patch(ctrl, chain, kc, bad);
+        bad = false;
+    }
     };
 
     if (DIM == 3 && plan.runs) {
@@ -895,12 +905,11 @@ __global__ __launch_bounds__(kFvThreads) void fv_lambda_kernel(const T *__restri
     }
 }
 
-__global__ void ctrl_init_kernel(Ctrl *ctrl)
+// n words to zero with vector stores (no memset node, so this is safe inside
+// captured graphs)
+__global__ void zero_kernel(unsigned *w, int n)
 {
-    // zero the whole control block with vector stores (no memset node, so
-    // this is safe inside captured graphs)
-    unsigned long long *w = reinterpret_cast<unsigned long long *>(ctrl);
-    for (int i = threadIdx.x; i < (int)(sizeof(Ctrl) / 8); i += blockDim.x) w[i] = 0ull;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) w[i] = 0u;
 }
 
 // ------------------------------------------------------------------ host --
@@ -922,12 +931,15 @@ pb_status device_cus(int *out)
     return PB_OK;
 }
 
-FvChain fv_chain(const pb_batch *b, int step, double cfl)
+FvChain fv_chain(const pb_batch *b, int step, double cfl, bool by_patch)
 {
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
+    // the set alternates with the state buffer that the step reads
+    auto set = [&](int i) { return reinterpret_cast<unsigned *>(b->ws + L.seen) + (size_t)i * seen_words(b->K); };
     return FvChain{step, cfl, b->dxmin, reinterpret_cast<unsigned long long *>(b->ws + L.lines), L.n_lines,
                    reinterpret_cast<const double *>(b->ws + L.part),
-                   b->pde == PB_PDE_SRHD ? c2p_units(b) : std::min(b->K, kLamUnits)};
+                   b->pde == PB_PDE_SRHD ? c2p_units(b) : std::min(b->K, kLamUnits),
+                   by_patch ? set(b->cur ^ (step & 1)) : nullptr, set(b->cur ^ (step & 1) ^ 1), seen_words(b->K)};
 }
 
 namespace {
@@ -942,7 +954,7 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
     Ctrl *ctrl = reinterpret_cast<Ctrl *>(b->ws);
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
     // in CFL mode the steps of a call hand the speed maxima to each other
-    const FvChain chain = fv_chain(b, step, cfl);
+    const FvChain chain = fv_chain(b, step, cfl, DIM == 3 && b->fv_runs.w < 0);
     const T *qi = static_cast<const T *>(qin);
     T *qo = static_cast<T *>(qout);
     const double *ex = Ph::E ? reinterpret_cast<const double *>(b->ws + L.pres)
@@ -1266,7 +1278,18 @@ pb_status launch_fv_lambda(pb_batch *b, const void *q, hipStream_t s)
 
 pb_status launch_ctrl_init(pb_batch *b, hipStream_t s)
 {
-    hipLaunchKernelGGL(ctrl_init_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<Ctrl *>(b->ws));
+    hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<unsigned *>(b->ws),
+                       (int)(sizeof(Ctrl) / 4));
+    PB_HIP(hipGetLastError());
+    return launch_seen_init(b, s);
+}
+
+pb_status launch_seen_init(pb_batch *b, hipStream_t s)
+{
+    const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
+    const int n = 2 * seen_words(b->K);
+    hipLaunchKernelGGL(zero_kernel, dim3(std::min((n + 255) / 256, 256)), dim3(256), 0, s,
+                       reinterpret_cast<unsigned *>(b->ws + L.seen), n);
     PB_HIP(hipGetLastError());
     return PB_OK;
 }

@@ -254,6 +254,7 @@ pb_status pb_autotune(pb_batch *b, int32_t kind, double cfl, double dt_fixed, do
     if (e1) (void)hipEventDestroy(e1);
     // restore the control block whatever happened
     hipError_t er = hipMemcpyAsync(b->ws, &saved, sizeof(Ctrl), hipMemcpyHostToDevice, s);
+    if (const pb_status si = launch_seen_init(b, s); st == PB_OK) st = si;
     if (er == hipSuccess) er = hipStreamSynchronize(s);
     if (st != PB_OK) {
         (void)pb_batch_set_tuning(b, &before);   // (also drops graphs that hold an older run table)
