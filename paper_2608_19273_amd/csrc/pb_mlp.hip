@@ -20,7 +20,7 @@
 #include "pb_mlp.h"
 
 namespace pb {
-constexpr int kTrainWavesMax = 256;   // partial-gradient rows (waves of one training call)
+constexpr int kTrainWavesMax = 256;   // partial-gradient rows (work-groups of one training call)
 constexpr int kPartStride = 4672;     // floats per partial row: kMlpNParam + the loss, padded to 64
 static_assert(kPartStride >= kMlpNParam + 1 && kPartStride % 64 == 0, "partial row");
 constexpr int kStatBlocks = 256;      // work-groups of the statistics passes
@@ -123,9 +123,11 @@ __global__ __launch_bounds__(kT, 4) void mlp_forward_kernel(MlpDev m, const floa
 
 // ---------------------------------------------------------------- training
 //
-// One wave per chunk of 64 rows (samples are the columns of the 16x16 tiles,
-// hidden units the rows, as in inference).  Forward: the inference layers on
-// the matrix cores, keeping the bf16 hidden activations h1, h2 (D tiles).
+// Four waves per chunk of 64 rows: samples are the columns of the 16x16 tiles,
+// hidden units the rows, as in inference, and wave w of the four takes the
+// samples 16 w .. 16 w + 15 forward and backward, then the rows 16 w .. of the
+// weight gradients.  Forward: the inference layers on the matrix cores,
+// keeping the bf16 hidden activations h1, h2 (D tiles).
 // Backward (the bf16 rounding treated as the identity, ReLU masks h > 0):
 //   dy   = 2 (y - t) / n,
 //   dh2  = dy w3 (h2 > 0)                 (VALU, in the D tiles),
@@ -135,10 +137,16 @@ __global__ __launch_bounds__(kT, 4) void mlp_forward_kernel(MlpDev m, const floa
 //          dh2, dh1, h1 and xb are staged transposed in LDS),
 //   gw3 = h2 dy, gb2 = sum dh2, gb1 = sum dh1, gb3 = sum dy  (FP32 VALU).
 // Products on the matrix cores take bf16 operands (dh1 and dh2 rounded to
-// nearest even), accumulate in FP32.  Each wave adds its chunk's gradient
-// into its own row of the partial buffer (the row is written by that wave
-// only, chunk after chunk); the reduction sums the rows in a fixed order, so
-// gradients are bitwise reproducible.
+// nearest even), accumulate in FP32.  A work-group holds Q such groups of four
+// waves; each adds the gradients of its chunks in registers, chunk after
+// chunk, and the work-group adds its groups in order into its row of the
+// partial buffer; the reduction sums the rows in a fixed order, so gradients
+// are bitwise reproducible.
+// A chunk is one chain of dependent operations: with one wave for all of its
+// 64 columns, its gradient added to the row in global memory chunk by chunk, 8192
+// rows (128 chunks, one per CU) took 13.7 us here, 7.4 with four waves; 200000
+// rows took 279 us with the reduction and take 34.  (Four groups per
+// work-group spill at 128 registers: 200000 rows in 83 us.)
 constexpr int kLd = 72;               // LDS row stride (bf16) of the transposed staging (16-byte pad)
 
 // row map of a training call: identity (rows row0 + i) or the epoch's
@@ -190,24 +198,43 @@ __device__ __forceinline__ long long map_row(const RowMap &M, long long pos)
 __device__ __forceinline__ float bf16_lo(unsigned v) { return __uint_as_float(v << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned v) { return __uint_as_float(v & 0xFFFF0000u); }
 
-// sum over the 16 lanes of a lane group (lanes g*16 .. g*16+15)
+// v of the lane that a DPP control selects
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+// sum over the 16 lanes of a lane group (lanes g*16 .. g*16+15), in all of
+// them, on DPP moves: neighbours, pairs, the eight mirrored, the row mirrored
 __device__ __forceinline__ float group16_sum(float v)
 {
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 64);
+    v += dpp_f<0xb1>(v);
+    v += dpp_f<0x4e>(v);
+    v += dpp_f<0x141>(v);
+    v += dpp_f<0x140>(v);
     return v;
 }
 
-__global__ __launch_bounds__(64) void mlp_train_kernel(const MlpPack *__restrict__ P, const MlpTrainPack *__restrict__ TP,
-                                                       const float *__restrict__ par, const float *__restrict__ x,
-                                                       const float *__restrict__ tgt, long long n, RowMap rmap,
-                                                       float *__restrict__ part, int chunks_per_wave)
+struct TrainStage {
+    __attribute__((aligned(16))) unsigned short h1[kMlpHid * kLd], dh2[kMlpHid * kLd], dh1[kMlpHid * kLd], xb[16 * kLd];
+    float vec[4][3][kMlpHid];   // [wave][gb1, gb2, gw3][unit]: sums over the wave's samples
+    float dy[4], loss[4];
+};
+static_assert(sizeof(unsigned short) * kLd * (3 * kMlpHid + 16) >= sizeof(float) * (kMlpNParam + 1),
+              "a group's sums take its staging");
+
+template <int Q>
+__global__ __launch_bounds__(256 * Q) void mlp_train_kernel(const MlpPack *__restrict__ P,
+                                                            const MlpTrainPack *__restrict__ TP,
+                                                            const float *__restrict__ par, const float *__restrict__ x,
+                                                            const float *__restrict__ tgt, long long n, RowMap rmap,
+                                                            float *__restrict__ part, int rounds)
 {
-    __shared__ __attribute__((aligned(16))) unsigned short h1s[kMlpHid * kLd], dh2s[kMlpHid * kLd], dh1s[kMlpHid * kLd],
-        xbs[16 * kLd];
-    const int l = threadIdx.x, g = l >> 4, j = l & 15;
-    const int w = blockIdx.x;
-    float *prow = part + (long long)w * kPartStride;
+    __shared__ TrainStage stage[Q];
+    const int t = threadIdx.x & 255, q = Q > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, g = l >> 4, j = l & 15;
+    TrainStage &S = stage[q];
     float xm[kMlpIn], xi[kMlpIn];
 #pragma unroll
     for (int k = 0; k < kMlpIn; ++k) {
@@ -221,9 +248,15 @@ __global__ __launch_bounds__(64) void mlp_train_kernel(const MlpPack *__restrict
 #pragma unroll
         for (int i = 0; i < 4; ++i) w3r[mt][i] = bf16_val(bf16_rne(par[kOffW3 + 16 * mt + 4 * g + i]));
     const float inv_n2 = 2.0f / (float)n;
-    for (int c = 0; c < chunks_per_wave; ++c) {
-        const long long pos = ((long long)c * gridDim.x + w) * 64 + l;   // this lane's sample
-        if (((long long)c * gridDim.x + w) * 64 >= n) break;             // the same for the whole wave
+    // sums over the group's chunks: gW2 rows 16 w + 4 g + i, columns 16 mk + j;
+    // gW1 likewise; one unit of gb1, gb2 and gw3 each (threads below 192)
+    f32x4_t sw2[4], sw1 = {0.f, 0.f, 0.f, 0.f};
+    float svec = 0.f, sdy = 0.f, sloss = 0.f;
+#pragma unroll
+    for (int mk = 0; mk < 4; ++mk) sw2[mk] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    const int sc = 16 * w + j;   // this lane's sample of the chunk
+    for (int c = 0; c < rounds; ++c) {
+        const long long pos = (((long long)c * gridDim.x + blockIdx.x) * Q + q) * 64 + sc;
         const bool act = pos < n;
         const long long r = act ? map_row(rmap, pos) : 0;
         float z[kMlpIn];
@@ -231,220 +264,182 @@ __global__ __launch_bounds__(64) void mlp_train_kernel(const MlpPack *__restrict
         for (int k = 0; k < kMlpIn; ++k) z[k] = act ? (x[r * kMlpIn + k] - xm[k]) * xi[k] : 0.f;
         const float tv = act ? tgt[r] : 0.f;
         const unsigned p01 = pack_bf16(z[0], z[1]), p23 = pack_bf16(z[2], z[3]), p4 = pack_bf16(z[4], 0.f);
-        // xb transposed: row k (feature), column = sample
-        xbs[0 * kLd + l] = (unsigned short)(p01 & 0xFFFF);
-        xbs[1 * kLd + l] = (unsigned short)(p01 >> 16);
-        xbs[2 * kLd + l] = (unsigned short)(p23 & 0xFFFF);
-        xbs[3 * kLd + l] = (unsigned short)(p23 >> 16);
-        xbs[4 * kLd + l] = (unsigned short)(p4 & 0xFFFF);
-#pragma unroll
-        for (int k = 5; k < 16; ++k) xbs[k * kLd + l] = 0;
-        // ---- forward (as inference, all four column tiles) ----
-        unsigned h1[4][8], h2[4][8];
+        // xb transposed: row k (feature), column = sample; group g writes rows 4 g ..
+        const unsigned lo = g == 0 ? p01 : (g == 1 ? p4 : 0u), hi = g == 0 ? p23 : 0u;
+        S.xb[(4 * g + 0) * kLd + sc] = (unsigned short)(lo & 0xFFFF);
+        S.xb[(4 * g + 1) * kLd + sc] = (unsigned short)(lo >> 16);
+        S.xb[(4 * g + 2) * kLd + sc] = (unsigned short)(hi & 0xFFFF);
+        S.xb[(4 * g + 3) * kLd + sc] = (unsigned short)(hi >> 16);
+        // ---- forward (as inference, this wave's column tile) ----
+        unsigned h1[8], h2[8];
+        const bf16x4_t bx = __builtin_bit_cast(bf16x4_t, (u32x2_t){lo, hi});
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
-            const bf16x4_t w1 = P->w1[mt][l];
             const f32x4_t b1 = *reinterpret_cast<const f32x4_t *>(&P->b1[16 * mt + 4 * g]);
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int src = 16 * nt + j;
-                const unsigned a01 = __shfl(p01, src, 64), a23 = __shfl(p23, src, 64), a4 = __shfl(p4, src, 64);
-                const unsigned lo = g == 0 ? a01 : (g == 1 ? a4 : 0u), hi = g == 0 ? a23 : 0u;
-                const bf16x4_t bx = __builtin_bit_cast(bf16x4_t, (u32x2_t){lo, hi});
-                const f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w1, bx, b1, 0, 0, 0);
-                h1[nt][2 * mt] = pack_relu(d[0], d[1]);
-                h1[nt][2 * mt + 1] = pack_relu(d[2], d[3]);
-            }
+            const f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(P->w1[mt][l], bx, b1, 0, 0, 0);
+            h1[2 * mt] = pack_relu(d[0], d[1]);
+            h1[2 * mt + 1] = pack_relu(d[2], d[3]);
         }
+        const bf16x8_t k0 = __builtin_bit_cast(bf16x8_t, (u32x4_t){h1[0], h1[1], h1[2], h1[3]});
+        const bf16x8_t k1 = __builtin_bit_cast(bf16x8_t, (u32x4_t){h1[4], h1[5], h1[6], h1[7]});
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
-            const bf16x8_t wa = P->w2[mt][0][l], wb = P->w2[mt][1][l];
             const f32x4_t b2 = *reinterpret_cast<const f32x4_t *>(&P->b2[16 * mt + 4 * g]);
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const bf16x8_t k0 = __builtin_bit_cast(bf16x8_t, (u32x4_t){h1[nt][0], h1[nt][1], h1[nt][2], h1[nt][3]});
-                const bf16x8_t k1 = __builtin_bit_cast(bf16x8_t, (u32x4_t){h1[nt][4], h1[nt][5], h1[nt][6], h1[nt][7]});
-                f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, k0, b2, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb, k1, d, 0, 0, 0);
-                h2[nt][2 * mt] = pack_relu(d[0], d[1]);
-                h2[nt][2 * mt + 1] = pack_relu(d[2], d[3]);
-            }
+            f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P->w2[mt][0][l], k0, b2, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P->w2[mt][1][l], k1, d, 0, 0, 0);
+            h2[2 * mt] = pack_relu(d[0], d[1]);
+            h2[2 * mt + 1] = pack_relu(d[2], d[3]);
         }
-        float y = 0.f;
+        float y;
         {
-            const bf16x8_t w3a = P->w3[0][l], w3b = P->w3[1][l];
             const float b3 = P->b3;
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const bf16x8_t q0 = __builtin_bit_cast(bf16x8_t, (u32x4_t){h2[nt][0], h2[nt][1], h2[nt][2], h2[nt][3]});
-                const bf16x8_t q1 = __builtin_bit_cast(bf16x8_t, (u32x4_t){h2[nt][4], h2[nt][5], h2[nt][6], h2[nt][7]});
-                f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3a, q0, (f32x4_t){b3, b3, b3, b3}, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w3b, q1, d, 0, 0, 0);
-                if (g == nt) y = d[0];
-            }
+            const bf16x8_t q0 = __builtin_bit_cast(bf16x8_t, (u32x4_t){h2[0], h2[1], h2[2], h2[3]});
+            const bf16x8_t q1 = __builtin_bit_cast(bf16x8_t, (u32x4_t){h2[4], h2[5], h2[6], h2[7]});
+            f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P->w3[0][l], q0, (f32x4_t){b3, b3, b3, b3}, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(P->w3[1][l], q1, d, 0, 0, 0);
+            y = d[0];   // every row is the output
         }
         const float dlt = act ? y - tv : 0.f;
         const float dy = dlt * inv_n2;
-        // ---- backward: dh2 (D tiles), gw3 and gb2 partials, staging ----
-        unsigned dh2p[4][8];
-        float gw3[4][4], gb2[4][4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) gw3[mt][i] = gb2[mt][i] = 0.f;
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const float dyn = __shfl(dy, 16 * nt + j, 64);
-#pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
-                float hv[4], dv[4];
-                hv[0] = bf16_lo(h2[nt][2 * mt]);
-                hv[1] = bf16_hi(h2[nt][2 * mt]);
-                hv[2] = bf16_lo(h2[nt][2 * mt + 1]);
-                hv[3] = bf16_hi(h2[nt][2 * mt + 1]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    dv[i] = hv[i] > 0.f ? dyn * w3r[mt][i] : 0.f;
-                    gw3[mt][i] = fmaf(dyn, hv[i], gw3[mt][i]);
-                    gb2[mt][i] += dv[i];
-                }
-                dh2p[nt][2 * mt] = pack_bf16(dv[0], dv[1]);
-                dh2p[nt][2 * mt + 1] = pack_bf16(dv[2], dv[3]);
-                // transposed staging: row = unit, column = sample 16 nt + j
-                const int u = 16 * mt + 4 * g, sc = 16 * nt + j;
-                dh2s[(u + 0) * kLd + sc] = (unsigned short)(dh2p[nt][2 * mt] & 0xFFFF);
-                dh2s[(u + 1) * kLd + sc] = (unsigned short)(dh2p[nt][2 * mt] >> 16);
-                dh2s[(u + 2) * kLd + sc] = (unsigned short)(dh2p[nt][2 * mt + 1] & 0xFFFF);
-                dh2s[(u + 3) * kLd + sc] = (unsigned short)(dh2p[nt][2 * mt + 1] >> 16);
-                h1s[(u + 0) * kLd + sc] = (unsigned short)(h1[nt][2 * mt] & 0xFFFF);
-                h1s[(u + 1) * kLd + sc] = (unsigned short)(h1[nt][2 * mt] >> 16);
-                h1s[(u + 2) * kLd + sc] = (unsigned short)(h1[nt][2 * mt + 1] & 0xFFFF);
-                h1s[(u + 3) * kLd + sc] = (unsigned short)(h1[nt][2 * mt + 1] >> 16);
-            }
-        }
-        // ---- dh1 = (W2^T dh2) (h1 > 0), gb1 partial, staging ----
-        float gb1[4][4];
+        // ---- backward: dh2 (D tiles), staging, gw3 and gb2 over the wave's samples ----
+        unsigned dh2p[8];
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) {
-            const bf16x8_t wa = TP->w2t[mt][0][l], wb = TP->w2t[mt][1][l];
+            float hv[4], dv[4];
+            hv[0] = bf16_lo(h2[2 * mt]);
+            hv[1] = bf16_hi(h2[2 * mt]);
+            hv[2] = bf16_lo(h2[2 * mt + 1]);
+            hv[3] = bf16_hi(h2[2 * mt + 1]);
+            const int u = 16 * mt + 4 * g;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) gb1[mt][i] = 0.f;
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const bf16x8_t k0 = __builtin_bit_cast(bf16x8_t, (u32x4_t){dh2p[nt][0], dh2p[nt][1], dh2p[nt][2], dh2p[nt][3]});
-                const bf16x8_t k1 = __builtin_bit_cast(bf16x8_t, (u32x4_t){dh2p[nt][4], dh2p[nt][5], dh2p[nt][6], dh2p[nt][7]});
-                f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, k0, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb, k1, d, 0, 0, 0);
-                float hv[4];
-                hv[0] = bf16_lo(h1[nt][2 * mt]);
-                hv[1] = bf16_hi(h1[nt][2 * mt]);
-                hv[2] = bf16_lo(h1[nt][2 * mt + 1]);
-                hv[3] = bf16_hi(h1[nt][2 * mt + 1]);
-                float dv[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    dv[i] = hv[i] > 0.f ? d[i] : 0.f;
-                    gb1[mt][i] += dv[i];
-                }
-                const unsigned q0 = pack_bf16(dv[0], dv[1]), q1 = pack_bf16(dv[2], dv[3]);
-                const int u = 16 * mt + 4 * g, sc = 16 * nt + j;
-                dh1s[(u + 0) * kLd + sc] = (unsigned short)(q0 & 0xFFFF);
-                dh1s[(u + 1) * kLd + sc] = (unsigned short)(q0 >> 16);
-                dh1s[(u + 2) * kLd + sc] = (unsigned short)(q1 & 0xFFFF);
-                dh1s[(u + 3) * kLd + sc] = (unsigned short)(q1 >> 16);
-            }
-        }
-        __syncthreads();   // one wave: its LDS writes are visible to its reads after this
-        // ---- gW2 = dh2 h1^T and gW1 = dh1 xb^T on the matrix cores (K = samples) ----
-        const bool first = c == 0;
-#pragma unroll
-        for (int mu = 0; mu < 4; ++mu) {
-            const bf16x8_t a0 = *reinterpret_cast<const bf16x8_t *>(&dh2s[(16 * mu + j) * kLd + 8 * g]);
-            const bf16x8_t a1 = *reinterpret_cast<const bf16x8_t *>(&dh2s[(16 * mu + j) * kLd + 32 + 8 * g]);
-#pragma unroll
-            for (int mk = 0; mk < 4; ++mk) {
-                const bf16x8_t b0 = *reinterpret_cast<const bf16x8_t *>(&h1s[(16 * mk + j) * kLd + 8 * g]);
-                const bf16x8_t b1 = *reinterpret_cast<const bf16x8_t *>(&h1s[(16 * mk + j) * kLd + 32 + 8 * g]);
-                f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b0, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, d, 0, 0, 0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float *dst = prow + kOffW2 + (16 * mu + 4 * g + i) * kMlpHid + 16 * mk + j;
-                    *dst = first ? d[i] : *dst + d[i];
-                }
-            }
-            const bf16x8_t e0 = *reinterpret_cast<const bf16x8_t *>(&dh1s[(16 * mu + j) * kLd + 8 * g]);
-            const bf16x8_t e1 = *reinterpret_cast<const bf16x8_t *>(&dh1s[(16 * mu + j) * kLd + 32 + 8 * g]);
-            const bf16x8_t f0 = *reinterpret_cast<const bf16x8_t *>(&xbs[j * kLd + 8 * g]);
-            const bf16x8_t f1 = *reinterpret_cast<const bf16x8_t *>(&xbs[j * kLd + 32 + 8 * g]);
-            f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e0, f0, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e1, f1, d, 0, 0, 0);
-            if (j < kMlpIn) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float *dst = prow + kOffW1 + (16 * mu + 4 * g + i) * kMlpIn + j;
-                    *dst = first ? d[i] : *dst + d[i];
-                }
-            }
-        }
-        // ---- bias and w3 partials: sums over the 16 lanes of a group ----
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
+            for (int i = 0; i < 4; ++i) dv[i] = hv[i] > 0.f ? dy * w3r[mt][i] : 0.f;
+            dh2p[2 * mt] = pack_bf16(dv[0], dv[1]);
+            dh2p[2 * mt + 1] = pack_bf16(dv[2], dv[3]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float s1 = group16_sum(gb1[mt][i]), s2 = group16_sum(gb2[mt][i]), s3 = group16_sum(gw3[mt][i]);
+                // transposed staging: row = unit, column = sample
+                S.dh2[(u + i) * kLd + sc] = (unsigned short)(dh2p[2 * mt + i / 2] >> (16 * (i & 1)));
+                S.h1[(u + i) * kLd + sc] = (unsigned short)(h1[2 * mt + i / 2] >> (16 * (i & 1)));
+                const float s2 = group16_sum(dv[i]), s3 = group16_sum(dy * hv[i]);
                 if (j == i) {
-                    const int u = 16 * mt + 4 * g + i;
-                    float *d1 = prow + kOffB1 + u, *d2 = prow + kOffB2 + u, *d3 = prow + kOffW3 + u;
-                    *d1 = first ? s1 : *d1 + s1;
-                    *d2 = first ? s2 : *d2 + s2;
-                    *d3 = first ? s3 : *d3 + s3;
+                    S.vec[w][1][u + i] = s2;
+                    S.vec[w][2][u + i] = s3;
                 }
             }
-        float sdy = dy, sl = dlt * dlt;
+        }
+        // ---- dh1 = (W2^T dh2) (h1 > 0), staging, gb1 ----
+        const bf16x8_t e0 = __builtin_bit_cast(bf16x8_t, (u32x4_t){dh2p[0], dh2p[1], dh2p[2], dh2p[3]});
+        const bf16x8_t e1 = __builtin_bit_cast(bf16x8_t, (u32x4_t){dh2p[4], dh2p[5], dh2p[6], dh2p[7]});
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            sdy += __shfl_xor(sdy, o, 64);
-            sl += __shfl_xor(sl, o, 64);
+        for (int mt = 0; mt < 4; ++mt) {
+            f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(TP->w2t[mt][0][l], e0, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 0,
+                                                                0, 0);
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(TP->w2t[mt][1][l], e1, d, 0, 0, 0);
+            float hv[4], dv[4];
+            hv[0] = bf16_lo(h1[2 * mt]);
+            hv[1] = bf16_hi(h1[2 * mt]);
+            hv[2] = bf16_lo(h1[2 * mt + 1]);
+            hv[3] = bf16_hi(h1[2 * mt + 1]);
+            const int u = 16 * mt + 4 * g;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dv[i] = hv[i] > 0.f ? d[i] : 0.f;
+            const unsigned q0 = pack_bf16(dv[0], dv[1]), q1 = pack_bf16(dv[2], dv[3]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                S.dh1[(u + i) * kLd + sc] = (unsigned short)((i < 2 ? q0 : q1) >> (16 * (i & 1)));
+                const float s1 = group16_sum(dv[i]);
+                if (j == i) S.vec[w][0][u + i] = s1;
+            }
         }
+        const float dyw = group16_sum(dy), lw = group16_sum(dlt * dlt);   // the same in the four lane groups
         if (l == 0) {
-            prow[kOffB3] = first ? sdy : prow[kOffB3] + sdy;
-            prow[kMlpNParam] = first ? sl : prow[kMlpNParam] + sl;
+            S.dy[w] = dyw;
+            S.loss[w] = lw;
         }
+        __syncthreads();
+        // ---- gW2 = dh2 h1^T and gW1 = dh1 xb^T on the matrix cores (K = samples) ----
+        const int row = (16 * w + j) * kLd + 8 * g;
+        const bf16x8_t a0 = *reinterpret_cast<const bf16x8_t *>(&S.dh2[row]);
+        const bf16x8_t a1 = *reinterpret_cast<const bf16x8_t *>(&S.dh2[row + 32]);
+#pragma unroll
+        for (int mk = 0; mk < 4; ++mk) {
+            const bf16x8_t c0 = *reinterpret_cast<const bf16x8_t *>(&S.h1[(16 * mk + j) * kLd + 8 * g]);
+            const bf16x8_t c1 = *reinterpret_cast<const bf16x8_t *>(&S.h1[(16 * mk + j) * kLd + 32 + 8 * g]);
+            f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, c0, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            sw2[mk] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, c1, d, 0, 0, 0);
+        }
+        {
+            const bf16x8_t a2 = *reinterpret_cast<const bf16x8_t *>(&S.dh1[row]);
+            const bf16x8_t a3 = *reinterpret_cast<const bf16x8_t *>(&S.dh1[row + 32]);
+            const bf16x8_t f0 = *reinterpret_cast<const bf16x8_t *>(&S.xb[j * kLd + 8 * g]);
+            const bf16x8_t f1 = *reinterpret_cast<const bf16x8_t *>(&S.xb[j * kLd + 32 + 8 * g]);
+            f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2, f0, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            sw1 += __builtin_amdgcn_mfma_f32_16x16x32_bf16(a3, f1, d, 0, 0, 0);
+        }
+        // the four waves' bias and w3 sums, in order
+        if (t < 3 * kMlpHid) {
+            const float *v = &S.vec[0][0][t];
+            svec += ((v[0] + v[3 * kMlpHid]) + v[6 * kMlpHid]) + v[9 * kMlpHid];
+        }
+        sdy += ((S.dy[0] + S.dy[1]) + S.dy[2]) + S.dy[3];
+        sloss += ((S.loss[0] + S.loss[1]) + S.loss[2]) + S.loss[3];
         __syncthreads();   // the staging is rewritten by the next chunk
+    }
+    // the group's sums: to the work-group's row, or (Q > 1) first to the
+    // group's staging
+    float *dst = Q > 1 ? reinterpret_cast<float *>(&S) : part + (long long)blockIdx.x * kPartStride;
+#pragma unroll
+    for (int mk = 0; mk < 4; ++mk)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dst[kOffW2 + (16 * w + 4 * g + i) * kMlpHid + 16 * mk + j] = sw2[mk][i];
+    if (j < kMlpIn) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dst[kOffW1 + (16 * w + 4 * g + i) * kMlpIn + j] = sw1[i];
+    }
+    if (t < 3 * kMlpHid) dst[(t < kMlpHid ? kOffB1 : t < 2 * kMlpHid ? kOffB2 : kOffW3) + (t & (kMlpHid - 1))] = svec;
+    if (t == 0) {
+        dst[kOffB3] = sdy;
+        dst[kMlpNParam] = sloss;
+    }
+    if (Q > 1) {
+        __syncthreads();
+        float *prow = part + (long long)blockIdx.x * kPartStride;
+        for (int i = threadIdx.x; i <= kMlpNParam; i += 256 * Q) {
+            float v = reinterpret_cast<const float *>(&stage[0])[i];
+#pragma unroll
+            for (int k = 1; k < Q; ++k) v += reinterpret_cast<const float *>(&stage[k])[i];
+            prow[i] = v;
+        }
     }
 }
 
 // grad = fixed-order sum of the partial rows; loss = their loss sum / n
 // (added to *loss_acc when given); optionally one bias-corrected Adam step
-// on the masters.  A work-group takes 64 parameters; its four waves sum the
-// rows r = q (mod 4) (q the wave) in four interleaved accumulators each, and
-// wave 0 adds the four wave sums in order: the same order for every call
-// with the same row count.
-constexpr int kRedParams = 64;
-__global__ __launch_bounds__(256) void mlp_reduce_adam_kernel(const float *__restrict__ part, int rows, long long n,
-                                                              float *__restrict__ grad, float *__restrict__ loss,
-                                                              double *__restrict__ loss_acc, float *__restrict__ par,
-                                                              float *__restrict__ mo, float *__restrict__ vo, int adam,
-                                                              float lr, float b1, float b2, float eps, float bc1,
-                                                              float bc2)
+// on the masters.  A work-group takes 64 parameters; its 16 waves sum the
+// rows r = q (mod 16) (q the wave), all of a wave's loads in flight (128 rows:
+// 3.0 us, 6.3 with four waves of serial loads), and wave 0 adds the wave sums
+// in order: the same order for every call with the same row count.
+constexpr int kRedParams = 64, kRedWaves = 16;
+__global__ __launch_bounds__(64 * kRedWaves) void mlp_reduce_adam_kernel(
+    const float *__restrict__ part, int rows, long long n, float *__restrict__ grad, float *__restrict__ loss,
+    double *__restrict__ loss_acc, float *__restrict__ par, float *__restrict__ mo, float *__restrict__ vo, int adam,
+    float lr, float b1, float b2, float eps, float bc1, float bc2)
 {
-    __shared__ float red[4][kRedParams];
+    __shared__ float red[kRedWaves][kRedParams];
+    constexpr int R = kTrainWavesMax / kRedWaves;
     const int q = threadIdx.x >> 6, j = threadIdx.x & 63;
-    const int pi = blockIdx.x * kRedParams + j;
-    float a[4] = {0.f, 0.f, 0.f, 0.f};
-    if (pi <= kMlpNParam) {
-        int r = q;
-        for (; r + 12 < rows; r += 16) {
+    const int pi = blockIdx.x * kRedParams + j;   // below kPartStride (the rows' padding is read, not used)
+    float v[R], a = 0.f;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] += part[(long long)(r + 4 * u) * kPartStride + pi];
-        }
-        for (int u = 0; r < rows; r += 4, ++u) a[u & 3] += part[(long long)r * kPartStride + pi];
-    }
-    red[q][j] = (a[0] + a[1]) + (a[2] + a[3]);
+    for (int u = 0; u < R; ++u) v[u] = part[(long long)min(q + kRedWaves * u, rows - 1) * kPartStride + pi];
+#pragma unroll
+    for (int u = 0; u < R; ++u) a += q + kRedWaves * u < rows ? v[u] : 0.f;
+    red[q][j] = a;
     __syncthreads();
     if (q != 0 || pi > kMlpNParam) return;
-    const float gsum = ((red[0][j] + red[1][j]) + red[2][j]) + red[3][j];
+    float gsum = red[0][j];
+#pragma unroll
+    for (int u = 1; u < kRedWaves; ++u) gsum += red[u][j];
     if (pi == kMlpNParam) {
         const float L = gsum / (float)n;
         loss[0] = L;
@@ -600,17 +595,23 @@ pb_status run_grad_into(pb_mlp *m, float *part, float *grad, float *loss, const 
                         const RowMap &rmap, hipStream_t s, int adam, float lr, float b1, float b2, float eps, int step,
                         double *loss_acc)
 {
+    // one chunk of 64 rows per group of four waves as long as the partial rows
+    // last, then two groups per work-group (20000 rows: 14 us with the
+    // reduction against 49 with one wave per chunk), then more chunks per group
     const long long nchunks = (n + 63) / 64;
-    const int waves = (int)std::min<long long>(kTrainWavesMax, nchunks);
-    const int cpw = (int)((nchunks + waves - 1) / waves);
-    hipLaunchKernelGGL(mlp_train_kernel, dim3(waves), dim3(64), 0, s, m->pack, m->tpack, m->par, x, t, n, rmap, part,
-                       cpw);
+    const int Q = nchunks <= kTrainWavesMax ? 1 : 2;
+    const int rows = (int)std::min<long long>(kTrainWavesMax, (nchunks + Q - 1) / Q);
+    const int rounds = (int)((nchunks + (long long)rows * Q - 1) / ((long long)rows * Q));
+    auto train = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(rows), dim3(256 * Q), 0, s, m->pack, m->tpack, m->par, x, t, n, rmap, part,
+                           rounds);
+    };
+    Q == 1 ? train(mlp_train_kernel<1>) : train(mlp_train_kernel<2>);
     PB_HIP(hipGetLastError());
     const float bc1 = adam ? 1.f - std::pow(b1, (float)step) : 1.f;
     const float bc2 = adam ? 1.f - std::pow(b2, (float)step) : 1.f;
-    hipLaunchKernelGGL(mlp_reduce_adam_kernel, dim3((kMlpNParam + 1 + kRedParams - 1) / kRedParams), dim3(256), 0, s,
-                       part, waves, n,
-                       grad, loss, loss_acc, m->par, m->madam, m->vadam, adam, lr, b1, b2, eps, bc1, bc2);
+    hipLaunchKernelGGL(mlp_reduce_adam_kernel, dim3((kMlpNParam + 1 + kRedParams - 1) / kRedParams),
+                       dim3(64 * kRedWaves), 0, s, part, rows, n, grad, loss, loss_acc, m->par, m->madam, m->vadam, adam, lr, b1, b2, eps, bc1, bc2);
     PB_HIP(hipGetLastError());
     if (adam) return refresh(m, s);
     return PB_OK;
@@ -852,12 +853,9 @@ pb_status pb_mlp_grad(const pb_mlp *m, const void *x, const void *t, int64_t n, 
     pb_mlp *mm = const_cast<pb_mlp *>(m);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const RowMap ident{0, 0, 0ull, 0};
-    pb_status st = run_grad(mm, static_cast<const float *>(x), static_cast<const float *>(t), n, ident, s, 0, 0.f, 0.f,
-                            0.f, 0.f, 1, nullptr);
-    if (st != PB_OK) return st;
-    PB_HIP(hipMemcpyAsync(grad, mm->grad, kMlpNParam * sizeof(float), hipMemcpyDeviceToDevice, s));
-    PB_HIP(hipMemcpyAsync(loss, mm->loss, sizeof(float), hipMemcpyDeviceToDevice, s));
-    return PB_OK;
+    return run_grad_into(mm, mm->part, static_cast<float *>(grad), static_cast<float *>(loss),
+                         static_cast<const float *>(x), static_cast<const float *>(t), n, ident, s, 0, 0.f, 0.f, 0.f,
+                         0.f, 1, nullptr);
     PB_API_END
 }
 
