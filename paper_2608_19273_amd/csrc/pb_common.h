@@ -214,25 +214,29 @@ __device__ __forceinline__ double chain_dt(const double *lam, const FvChain &c)
     return c.cfl / den;
 }
 
-// largest value of each row of the partials [DIM][n_part], n_part <= MAXN, in
-// every thread
-template <int DIM, int MAXN>
+// largest value of each row of the partials [DIM][n_part], in each of the
+// work-group's T threads
+template <int DIM, int T>
 __device__ __forceinline__ void part_max(const FvChain &c, double *lam)
 {
-    __shared__ double red[DIM][kFvThreads / kWave];
+    __shared__ double red[DIM][T / kWave];
     const int t = threadIdx.x, lane = t & (kWave - 1);
-    // all loads in flight at once: past the end the last entry again
-    double v[DIM][MAXN / kFvThreads];
+    // eight loads per row in flight at a time: past the end the last entry again
+    for (int i0 = t; i0 < c.n_part + t; i0 += 8 * T) {
+        double v[DIM][8];
 #pragma unroll
-    for (int j = 0; j < MAXN / kFvThreads; ++j) {
-        const int i = min(t + j * kFvThreads, c.n_part - 1);
+        for (int j = 0; j < 8; ++j) {
+            const int i = min(i0 + j * T, c.n_part - 1);
 #pragma unroll
-        for (int d = 0; d < DIM; ++d) v[d][j] = c.part[d * c.n_part + i];
+            for (int d = 0; d < DIM; ++d) v[d][j] = c.part[d * c.n_part + i];
+        }
+#pragma unroll
+        for (int d = 0; d < DIM; ++d)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) lam[d] = fmax(lam[d], v[d][j]);
     }
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-#pragma unroll
-        for (int j = 0; j < MAXN / kFvThreads; ++j) lam[d] = fmax(lam[d], v[d][j]);
         lam[d] = wave_max(lam[d]);
         if (lane == 0) red[d][t / kWave] = lam[d];
     }
@@ -240,17 +244,18 @@ __device__ __forceinline__ void part_max(const FvChain &c, double *lam)
 #pragma unroll
     for (int d = 0; d < DIM; ++d)
 #pragma unroll
-        for (int w = 0; w < kFvThreads / kWave; ++w) lam[d] = fmax(lam[d], red[d][w]);
+        for (int w = 0; w < T / kWave; ++w) lam[d] = fmax(lam[d], red[d][w]);
 }
 
 // Adds the con2prim statistics of a step (rows 3-7 of its partials [8][n_part]:
 // iterations, failures, largest iteration count, fallbacks, cells) to the
 // control block; one work-group of the launch calls it.  Sums of integers
 // held exactly in doubles: the order does not matter.
+template <int T>
 __device__ __forceinline__ void add_c2p_stats(Ctrl *ctrl, const FvChain &c)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    for (int r = 3 + (int)threadIdx.x / kWave; r < 8; r += kFvThreads / kWave) {
+    for (int r = 3 + (int)threadIdx.x / kWave; r < 8; r += T / kWave) {
         double v = 0.0;
         for (int i = lane; i < c.n_part; i += kWave) {
             const double u = c.part[r * c.n_part + i];
@@ -273,23 +278,23 @@ __device__ __forceinline__ void add_c2p_stats(Ctrl *ctrl, const FvChain &c)
 // previous step of the call, or (kC2p: SRHD) from the partials of the con2prim
 // pass before it, whose statistics work-group 0 also adds up.  Every thread of
 // the work-group calls it.
-template <int DIM, bool kLam, bool kC2p = false>
+template <int DIM, bool kLam, bool kC2p = false, int T = kFvThreads>
 __device__ __forceinline__ double step_dt(Ctrl *ctrl, int slot_in, double dt_fixed, const FvChain &c)
 {
     double lam[DIM];
 #pragma unroll
     for (int d = 0; d < DIM; ++d) lam[d] = 0.0;
     if constexpr (kC2p) {
-        if (blockIdx.x == 0) add_c2p_stats(ctrl, c);
+        if (blockIdx.x == 0) add_c2p_stats<T>(ctrl, c);
         if (dt_fixed > 0.0) return dt_fixed;
-        part_max<DIM, kC2pUnits>(c, lam);
+        part_max<DIM, T>(c, lam);
         const double dt = chain_dt<DIM>(lam, c);
         if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->dt[slot_in] = dt;
         return dt;
     }
     if (!kLam) return dt_fixed;
     if (c.step == 0) {
-        part_max<DIM, kLamUnits>(c, lam);
+        part_max<DIM, T>(c, lam);
     } else {
         static_assert(kLines == 8, "one line per lane of eight");
         const int lane = threadIdx.x & (kWave - 1);
@@ -329,11 +334,11 @@ __device__ __forceinline__ double rk_base(double q0, double y1, double y2, doubl
 // records the step's dt for the host (see FvChain).  The exchange between the
 // lanes runs on DPP moves and the one barrier waits for LDS only, so that the
 // work-group's last stores drain after it has ended its own work.
-template <int DIM, bool kLam>
+template <int DIM, bool kLam, int T = kFvThreads>
 __device__ __forceinline__ void finish_step(Ctrl *ctrl, int slot_in, double dt, const double *lm, bool bad,
                                             const FvChain &c)
 {
-    constexpr int W = kFvThreads / kWave;
+    constexpr int W = T / kWave;
     __shared__ double red[DIM][W];
     __shared__ int sbad[W];
     const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
@@ -354,16 +359,16 @@ __device__ __forceinline__ void finish_step(Ctrl *ctrl, int slot_in, double dt, 
         if (kLam && blockIdx.x == 0) ctrl->dt[slot_in] = dt;
     }
     if (blockIdx.x == 0)
-        for (int i = t; i < c.n_seen; i += kFvThreads) c.seen_next[i] = 0u;
+        for (int i = t; i < c.n_seen; i += T) c.seen_next[i] = 0u;
     if (kLam && t < DIM) {
         double m = red[t][0];
         for (int i = 1; i < W; ++i) m = fmax(m, red[t][i]);
         atomicMax(c.lines + 16 * (c.step % 3 * c.n_lines + (blockIdx.x & (c.n_lines - 1))) + t,
                   (unsigned long long)__double_as_longlong(m));
     }
-    if (kLam && blockIdx.x == 0 && t >= kWave && t < kWave + c.n_lines) {
+    if (kLam && blockIdx.x == 0 && t < c.n_lines) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) c.lines[16 * ((c.step + 1) % 3 * c.n_lines + t - kWave) + d] = 0ull;
+        for (int d = 0; d < 3; ++d) c.lines[16 * ((c.step + 1) % 3 * c.n_lines + t) + d] = 0ull;
     }
 }
 

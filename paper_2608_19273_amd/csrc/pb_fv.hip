@@ -2,8 +2,9 @@
 // (the FV composition of paper Sec. II-A, Eq. (3): source term, face fluxes
 // from the two adjacent cell values, update), one launch per time step.
 //
-// Work decomposition (MI355X): a work-group of 256 threads owns one z-slab of
-// one patch and marches through it plane by plane.  Thread t owns column
+// Work decomposition (MI355X): a work-group of up to 256 threads (as many
+// waves as a plane fills) owns one z-slab of one patch or a run of planes and
+// marches through it plane by plane.  Thread t owns column
 // (x, y) = (t % p, t / p).  For each plane the work-group
 //   1. stores its cells' Q and per-cell aux (1/rho, p, c ...) in LDS, and the
 //      4p face-halo cells of the plane, read straight from the face
@@ -134,19 +135,23 @@ struct FvPlan {
     const int4 *runs;   // column mode (non-null): unit u marches runs[u] = (patch, first plane, planes)
 };
 
-template <class Ph, int DIM, typename T, bool kLam>
-__global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3))) void fv_step_kernel(
+// the largest p + 2 of a work-group of so many waves
+constexpr int kPlanePH[5] = {0, 10, 13, 15, kFvPmax + 2};
+
+template <class Ph, int DIM, typename T, bool kLam, int WV>
+__global__ __launch_bounds__(kWave *WV) __attribute__((amdgpu_waves_per_eu(3))) void fv_step_kernel(
     const T *__restrict__ qin, T *__restrict__ qout, const double *__restrict__ ex,
     const PatchDev *__restrict__ patches, FvPlan plan, Ctrl *__restrict__ ctrl, int slot_in, double dt_fixed, FvChain chain, Ph ph)
 {
     constexpr int N = Ph::N, A = Ph::A, AP = PlaneAux<Ph>::n, W = N + AP, AA = A > 0 ? A : 1;
-    constexpr int PH = kFvPmax + 2;
+    constexpr int PH = kPlanePH[WV];
+    constexpr bool kOneWave = WV < 4;
     constexpr int DZ = DIM == 3 ? 2 : 1;   // z direction index (unused in 2D)
     __shared__ double lds[2][W][PH * PH];
 
     const int t = threadIdx.x;
     const int unit = plan.remap ? xcd_remap(blockIdx.x, plan.n_units) : (int)blockIdx.x;
-    const double dt = step_dt<DIM, kLam, (Ph::E > 0)>(ctrl, slot_in, dt_fixed, chain);
+    const double dt = step_dt<DIM, kLam, (Ph::E > 0), kWave * WV>(ctrl, slot_in, dt_fixed, chain);
     double lm[3] = {0.0, 0.0, 0.0};
     bool bad = false;
     int parity = 0;   // LDS buffer of the next plane (alternates over every plane the work-group marches)
@@ -162,10 +167,13 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
     const int x = active ? t % p : 0, y = active ? t / p : 0;
     const int li = (y + 1) * PH + (x + 1);
 
-    // face-halo cell of each plane: wave w serves side w (-x, +x, -y, +y),
-    // so the extra loads and aux evaluations spread over all four waves
-    const int side = __builtin_amdgcn_readfirstlane(t >> 6), j = t & 63;
-    const bool halo = work && j < p;
+    // face-halo cell of each plane: of four waves, wave w serves side w (-x,
+    // +x, -y, +y), so the extra loads and aux evaluations spread over all of
+    // them; of fewer waves the last, which has lanes without a cell of their
+    // own, serves all 4p cells
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const int side = kOneWave ? lane / p : wave, j = kOneWave ? lane - side * p : lane;
+    const bool halo = work && (kOneWave ? wave == WV - 1 && side < 4 : j < p);
     int hsrc = 0, hdst = 0;
     if (halo) {
         int hx, hy, sx, sy;
@@ -178,14 +186,41 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
     }
     const long long cxy = (long long)y * p + x;
     const long long pp = (long long)p * p;
+    // where the halo cell of patch kk's plane 0 is: four waves, the first cell
+    // of the neighbour on the wave's side; one wave, the byte offset of the
+    // lane's cell from the state's start (32 bits, one register)
+    using HaloOff = std::conditional_t<kOneWave, unsigned, long long>;
+    auto halo_off = [&](int kk) -> HaloOff {
+        const PatchDev &Q = patches[kk];
+        if constexpr (!kOneWave) {
+            return patches[Q.nbr[side]].off;
+        } else {
+            const unsigned o0 = (unsigned)patches[Q.nbr[0]].off, o1 = (unsigned)patches[Q.nbr[1]].off,
+                           o2 = (unsigned)patches[Q.nbr[2]].off, o3 = (unsigned)patches[Q.nbr[3]].off;
+            const unsigned o = !halo || side == 0 ? o0 : side == 1 ? o1 : side == 2 ? o2 : o3;
+            return (o * N + hsrc) * (unsigned)sizeof(T);
+        }
+    };
+    auto halo_load = [&](HaloOff off, int z, RawCell<Ph, T> &r) {
+        if constexpr (!kOneWave) {
+            issue_load<Ph>(qin, ex, off, C, (long long)z * pp + hsrc, r);
+        } else {
+            const unsigned o = off + (unsigned)(z * (int)pp) * (unsigned)sizeof(T);
+#pragma unroll
+            for (int v = 0; v < N; ++v)
+                r.q[v] = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(qin + (long long)v * C) + o);
+        }
+    };
     int kc = k;
     // the current patch and its +z neighbour (the run's next patch): cell
     // offsets of the patch and of the wave's halo-side neighbour (lanes
     // without a halo cell load cell 0 of that neighbour and drop it)
-    long long offc = patches[k].off, hoffc = patches[patches[k].nbr[side]].off;
+    long long offc = patches[k].off;
+    HaloOff hoffc = halo_off(k);
     double hr_ = 0.5 * dt * patches[k].inv_dx;   // the face sums below are doubled
     int kn = (DIM == 3) ? patches[k].nbr[5] : k;
-    long long offn = patches[kn].off, hoffn = patches[patches[kn].nbr[side]].off;
+    long long offn = patches[kn].off;
+    HaloOff hoffn = halo_off(kn);
     int zl = z0;   // the current plane's z inside the current patch
 
     // per thread, two sets that swap roles from plane to plane (the loop runs
@@ -240,7 +275,7 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
         }
     }
     if (work) {
-        issue_load<Ph>(qin, ex, hoffc, C, z0 * pp + hsrc, hrA);
+        halo_load(hoffc, z0, hrA);
     }
 
     // run plane i (at zl of the current patch): consumes rn (own plane i+1)
@@ -255,7 +290,7 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
         unpack<Ph>(hr, hq, he);
         {
             const int zh = zl + min(1, n - 1 - i);
-            issue_load<Ph>(qin, ex, zh >= p ? hoffn : hoffc, C, (zh >= p ? zh - p : zh) * pp + hsrc, hr);
+            halo_load(zh >= p ? hoffn : hoffc, zh >= p ? zh - p : zh, hr);
         }
         if (halo) {
             double ha[AA];
@@ -358,7 +393,7 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
             hr_ = 0.5 * dt * patches[kn].inv_dx;
             kn = patches[kn].nbr[5];
             offn = patches[kn].off;
-            hoffn = patches[patches[kn].nbr[side]].off;
+            hoffn = halo_off(kn);
         }
     };
 
@@ -399,7 +434,7 @@ __global__ __launch_bounds__(kFvThreads) __attribute__((amdgpu_waves_per_eu(3)))
         const int z1 = (DIM == 3) ? min(p, z0 + plan.slab) : 1;
         segment(k, min(z0, z1), max(0, z1 - z0));
     }
-    finish_step<DIM, kLam>(ctrl, slot_in, dt, lm, bad, chain);
+    finish_step<DIM, kLam, kWave * WV>(ctrl, slot_in, dt, lm, bad, chain);
 }
 
 // ---------------------------------------------------------------------------
@@ -942,6 +977,24 @@ FvChain fv_chain(const pb_batch *b, int step, double cfl, bool by_patch)
                    by_patch ? set(b->cur ^ (step & 1)) : nullptr, set(b->cur ^ (step & 1) ^ 1), seen_words(b->K)};
 }
 
+// Waves of a plane-march work-group: as many as the largest plane fills, so
+// that small planes don't hold registers and LDS for waves without cells.
+// What bounds these planes is the chain from barrier to barrier, and more
+// work-groups per CU overlap more of them.  Five steps of 693 patches, us with
+// always four waves and with this, FP64: 13^3 234 and 227, 11^3 171 and 160,
+// 9^3 138 and 122, 7^3 96 and 70; FP32 storage: 204 and 172, 150 and 117, 128
+// and 93, 95 and 67.  The halo cells are then one wave's, each lane with a
+// neighbour of its own: 32-bit offsets keep that in registers (with 64-bit ones
+// 24 to 70 spilled, and 13^3 in FP64 took 259 us), so the state must be
+// smaller than 4 GiB.  SRHD stays with four waves: two offsets per lane (the
+// pressures), and its steps got slower (8^3 213 to 262 us).
+static int plane_waves(const pb_batch *b)
+{
+    if (b->dim != 3 || b->pde == PB_PDE_SRHD) return 4;
+    const size_t bytes = (size_t)b->total_cells * b->N * (b->storage == PB_STORE_FP32 ? 4 : 8);
+    return bytes >> 32 ? 4 : (b->pmax * b->pmax + kWave - 1) / kWave;
+}
+
 namespace {
 
 template <class Ph, int DIM, typename T>
@@ -990,6 +1043,7 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
     // the balanced plane schedule over the work-groups that are resident at
     // once (uniform p)
     FvPlan plan{n_units, n_slabs, slab, b->fv_xcd_remap, 0, nullptr};
+    const int wv = plane_waves(b);
     auto plane_kernel = [&](auto kern) -> pb_status {
         if (DIM == 3 && b->fv_runs.d) {   // (built for the current tuning only)
             plan.runs = static_cast<const int4 *>(b->fv_runs.d);
@@ -1003,14 +1057,24 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
             plan.planes = planes;
             plan.n_units = (int)std::min<long long>(slots, planes);
         }
-        n_units = plan.n_units;
-        launch_main(b, kern, dim3(plan.n_units), dim3(kFvThreads), 0, s, qi, qo, ex, b->d_patches, plan, ctrl,
+        launch_main(b, kern, dim3(plan.n_units), dim3(kWave * wv), 0, s, qi, qo, ex, b->d_patches, plan, ctrl,
                     slot_in, dt_fixed, chain, ph);
         return PB_OK;
     };
+    auto plane_waves_kernel = [&](auto lam) -> pb_status {
+        constexpr bool kLam = decltype(lam)::value;
+        if constexpr (DIM == 3 && Ph::E == 0) {
+            switch (wv) {
+            case 1: return plane_kernel(fv_step_kernel<Ph, DIM, T, kLam, 1>);
+            case 2: return plane_kernel(fv_step_kernel<Ph, DIM, T, kLam, 2>);
+            case 3: return plane_kernel(fv_step_kernel<Ph, DIM, T, kLam, 3>);
+            }
+        }
+        return plane_kernel(fv_step_kernel<Ph, DIM, T, kLam, 4>);
+    };
     pb_status lst = PB_OK;
     if constexpr (Ph::E > 0) {  // SRHD: dt comes from the con2prim pass
-        lst = plane_kernel(fv_step_kernel<Ph, DIM, T, false>);
+        lst = plane_waves_kernel(std::false_type());
     } else if (DIM == 3 && b->fv_dma && fv_dma_eligible(b)) {
         if (dt_fixed > 0.0)
             launch_main(b, fv_step_dma_kernel<Ph, T, false>, dim3(n_units), dim3(kFvThreads), 0, s, qi, qo,
@@ -1021,10 +1085,7 @@ pb_status launch_typed(pb_batch *b, const Ph &ph, const void *qin, void *qout, i
                                b->d_patches, n_units, n_slabs, slab, b->fv_xcd_remap, ctrl, slot_in, dt_fixed,
                                chain, ph);
     } else {
-        if (dt_fixed > 0.0)
-            lst = plane_kernel(fv_step_kernel<Ph, DIM, T, false>);
-        else
-            lst = plane_kernel(fv_step_kernel<Ph, DIM, T, true>);
+        lst = dt_fixed > 0.0 ? plane_waves_kernel(std::false_type()) : plane_waves_kernel(std::true_type());
     }
     if (lst != PB_OK) return lst;
     PB_HIP(hipGetLastError());
@@ -1217,7 +1278,12 @@ pb_status runs_prepare(pb_batch *b)
     // and 42.4; relativistic, 2048 of 16^3, 316 and 304 with the con2prim pass.
     const bool own = b->fv_slab == 0 && b->fv_persist == 0 && b->fv_column == 0 && !b->fv_dma && !fv_small_eligible(b) &&
                      b->pde != PB_PDE_LINSYM;
-    pb_status st = build_table(b, b->fv_runs, 0, own ? -3 : b->fv_column, b->dim == 3);
+    // Fewer waves per work-group (plane_waves): as many as make three waves per
+    // SIMD, but two of single waves, whose runs get too short (3072 patches of
+    // 8^3, us per step: 52.8 with twelve per CU, 40.4 with eight, 44.4 with
+    // six; 1728 of 11^3 in FP32 with six, five, four of two waves 38, 42, 41).
+    const int waves = plane_waves(b), per_cu = waves == 1 ? 8 : 12 / waves;
+    pb_status st = build_table(b, b->fv_runs, 0, own ? -per_cu : b->fv_column, b->dim == 3);
     if (st != PB_OK) return st;
     const bool fd = b->dim == 3 && b->pde == PB_PDE_EULER;
     int w = b->fd_column;
