@@ -277,7 +277,7 @@ __device__ __forceinline__ void c2p_pass(const double *__restrict__ q, double *_
         any = walk.more();
         cell = walk.next();
         load(cell);
-        const C2pIn in = c2p_setup(qv[0], qv[1], qv[2], qv[3], qv[4], gam);
+        const C2pIn in = c2p_setup<kLearned>(qv[0], qv[1], qv[2], qv[3], qv[4], gam);
         double p0 = in.hi;
         if constexpr (kLearned) p0 = mlp_guess(lds_fresh(*sp), L.xm, L.xi, L.ym, L.ys, in);   // whole wave
         if constexpr (kWarm) p0 = pprev;
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(kC2pThreads) void con2prim_kernel(
 #pragma unroll
         for (int v = 0; v < 5; ++v) qv[v] = cons[(long long)v * n + i];
     }
-    const C2pIn in = c2p_setup(qv[0], qv[1], qv[2], qv[3], qv[4], gam);
+    const C2pIn in = c2p_setup<false>(qv[0], qv[1], qv[2], qv[3], qv[4], gam);
     C2pStats s = {{0.0, 0.0, 0.0}, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (active) {
         const double p0 = GUESS == 2 ? p_prev[i] : in.hi;
