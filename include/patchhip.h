@@ -117,7 +117,9 @@ typedef struct pb_batch pb_batch;
 
 typedef struct {
     int64_t steps;               /* steps taken since create / reset */
-    int64_t nonfinite_units;     /* work units that produced a NaN/Inf value */
+    int64_t nonfinite_units;     /* work units that produced a NaN/Inf value
+                                    (patches where the library splits them
+                                    itself) */
     int64_t c2p_cells;           /* con2prim cell solves (SRHD) */
     int64_t c2p_failures;        /* cells that did not converge / bad input */
     int64_t c2p_iterations;      /* total Newton updates */
@@ -372,10 +374,12 @@ pb_status pb_stream_copy(const void *src, void *dst, size_t bytes, void *stream)
  * (last-bit differences), the others change nothing in the results. */
 typedef struct {
     int32_t fv_slab;          /* FV: z-planes per work-group.  0 = the library's
-                                 own split (column runs as for fv_column = 3,
-                                 no more of them than the device holds at
-                                 once), the default; unused where another
-                                 field asks for a split */
+                                 own split (column runs as for fv_column, no
+                                 more of them than the device holds at once:
+                                 3 per CU of 16^3 patches, more of smaller
+                                 ones, whose work-groups have fewer waves),
+                                 the default; unused where another field asks
+                                 for a split */
     int32_t fv_xcd_remap;     /* FV: 1 = group consecutive patches per XCD */
     int32_t fd_xcd_remap;     /* FD: 1 = each XCD takes a contiguous run of tiles
                                  (the tiles of one patch share its L2) */
