@@ -940,11 +940,12 @@ __global__ __launch_bounds__(kFvThreads) void fv_lambda_kernel(const T *__restri
     }
 }
 
-// n words to zero with vector stores (no memset node, so this is safe inside
-// captured graphs)
-__global__ void zero_kernel(unsigned *w, int n)
+// two ranges of words to zero with vector stores (no memset node, so this is
+// safe inside captured graphs)
+__global__ void zero_kernel(unsigned *a, int na, unsigned *b, int nb)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) w[i] = 0u;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < na + nb; i += gridDim.x * blockDim.x)
+        (i < na ? a[i] : b[i - na]) = 0u;
 }
 
 // ------------------------------------------------------------------ host --
@@ -1342,22 +1343,18 @@ pb_status launch_fv_lambda(pb_batch *b, const void *q, hipStream_t s)
     });
 }
 
-pb_status launch_ctrl_init(pb_batch *b, hipStream_t s)
-{
-    hipLaunchKernelGGL(zero_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<unsigned *>(b->ws),
-                       (int)(sizeof(Ctrl) / 4));
-    PB_HIP(hipGetLastError());
-    return launch_seen_init(b, s);
-}
-
-pb_status launch_seen_init(pb_batch *b, hipStream_t s)
+static pb_status launch_zero(pb_batch *b, bool ctrl, hipStream_t s)
 {
     const WsLayout L = ws_layout(b->pde, b->dim, b->h, b->total_cells, b->N, b->storage, b->K);
-    const int n = 2 * seen_words(b->K);
-    hipLaunchKernelGGL(zero_kernel, dim3(std::min((n + 255) / 256, 256)), dim3(256), 0, s,
-                       reinterpret_cast<unsigned *>(b->ws + L.seen), n);
+    const int na = ctrl ? (int)(sizeof(Ctrl) / 4) : 0, nb = 2 * seen_words(b->K);
+    hipLaunchKernelGGL(zero_kernel, dim3(std::min((na + nb + 255) / 256, 256)), dim3(256), 0, s,
+                       reinterpret_cast<unsigned *>(b->ws), na, reinterpret_cast<unsigned *>(b->ws + L.seen), nb);
     PB_HIP(hipGetLastError());
     return PB_OK;
 }
+
+pb_status launch_ctrl_init(pb_batch *b, hipStream_t s) { return launch_zero(b, true, s); }
+
+pb_status launch_seen_init(pb_batch *b, hipStream_t s) { return launch_zero(b, false, s); }
 
 }  // namespace pb
