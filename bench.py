@@ -715,7 +715,7 @@ def main():
     copy_gbs = attainable_copy(torch, pb)
     sha = kernel_source_sha(("pb_fv.hip", "pb_physics.h", "pb_common.h"))
     kernel = ("fv_step_dma_kernel<Euler<3>, double, true>" if h["tuning"]["fv_dma"]
-              else "fv_step_kernel<Euler<3>, 3, double, true>")
+              else "fv_step_kernel<Euler<3>, 3, double, true, 4>")
     traffic = load_traffic("fv_euler3d_2048x16c_fp64_traffic.json", sha, kernel)
     achieved = h["kernel_GBs"]
     result = {
