@@ -1277,8 +1277,10 @@ pb_status runs_prepare(pb_batch *b)
     // and with these runs: 8 patches 27.9 and 6.8, 64 28.7 and 11.0, 256 33.0
     // and 28.6, 1024 87.4 and 83.3, 2048 163 and 159; 1728 patches of 8^3 50.9
     // and 42.4; relativistic, 2048 of 16^3, 316 and 304 with the con2prim pass.
+    // (Larger patches than the plane kernels take have no split of their own:
+    // the batch exists, its steps are refused.)
     const bool own = b->fv_slab == 0 && b->fv_persist == 0 && b->fv_column == 0 && !b->fv_dma && !fv_small_eligible(b) &&
-                     b->pde != PB_PDE_LINSYM;
+                     b->pde != PB_PDE_LINSYM && b->pmax <= kFvPmax;
     // Fewer waves per work-group (plane_waves): as many as make three waves per
     // SIMD, but two of single waves, whose runs get too short (3072 patches of
     // 8^3, us per step: 52.8 with twelve per CU, 40.4 with eight, 44.4 with
@@ -1288,7 +1290,7 @@ pb_status runs_prepare(pb_batch *b)
     if (st != PB_OK) return st;
     const bool fd = b->dim == 3 && b->pde == PB_PDE_EULER;
     int w = b->fd_column;
-    if (fd && w == 2) {
+    if (fd && w == 2 && b->pmax <= kFvPmax) {
         // the default: runs shorter than a patch where the batch has fewer
         // patches than resident work-groups.  A step of 16^3 patches with
         // whole patches and with these runs: 1 patch 157 and 34 us, 64 168 and
