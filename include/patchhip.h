@@ -405,7 +405,8 @@ typedef struct {
                                  phase (fd_wg_per_cu applies to it); 0 and 1
                                  give bitwise equal results */
     int32_t fv_persist;       /* FV 3D, batches of one p (register kernel):
-                                 w in 1..8 = a grid of w work-groups per CU,
+                                 w in 1..8 = a grid of w work-groups per CU
+                                 (their waves: see fv_column),
                                  each marching an equal run of the batch's K*p
                                  planes (patch after patch): with w no larger
                                  than the work-groups a CU holds at once there
@@ -423,7 +424,13 @@ typedef struct {
                                  CU in total; a work-group marches its run
                                  across patch tops without a restart, so the
                                  plane below and above every patch top inside
-                                 a run is read once.  Takes precedence over
+                                 a run is read once.  A work-group has as many
+                                 waves as the batch's largest plane fills (one
+                                 up to 8x8 cells, two up to 11x11, three up to
+                                 13x13, else four; four also for SRHD and for
+                                 states of 4 GiB and more), and a CU holds
+                                 about twelve waves of them at once.  Takes
+                                 precedence over
                                  fv_persist and fv_slab; builds a small device
                                  table here (host call, PB_EHIP if that
                                  fails).  0 = off, the default.  Results
@@ -467,11 +474,15 @@ pb_status pb_column_runs(const pb_batch_desc *desc, int32_t kind, int32_t w, int
  * kind 0 = the finite-volume step (fv_rusanov_step with the given cfl /
  * dt_fixed), kind 1 = one FD4+KO6 stage (fd_ko_step with sigma_ko; cfl /
  * dt_fixed as there; the linear system or 3D Euler).  Candidates:
- *   FV 3D: fv_column {3, 2} x fv_xcd_remap {1, 0}, then fv_persist 3 x
- *          fv_xcd_remap {1, 0} (batches of one p), then fv_slab in
+ *   FV 3D: the library's own split (fv_slab, fv_persist and fv_column 0) x
+ *          fv_xcd_remap {1, 0} where its runs are not those of a column
+ *          candidate, then fv_column {3, 2} x fv_xcd_remap {1, 0}, fv_persist
+ *          3 x fv_xcd_remap {1, 0} (batches of one p) (where work-groups have
+ *          fewer than four waves, see fv_column: fv_column {8, 4}, fv_persist
+ *          4, 6 or 8 for three, two or one), then fv_slab in
  *          {p_max, p_max/2, p_max/4} (>= 2) x fv_xcd_remap {1, 0}, then the
  *          DMA-fed kernel with fv_slab in {p_max, p_max/2} x fv_xcd_remap
- *          {1, 0} where it applies;
+ *          {1, 0} where it applies; the first PB_TUNE_MAX of these;
  *          a batch of one p with p^3 <= 256 runs the small-patch kernel,
  *          which has no launch-shape choice: one candidate, the current one;
  *   FV 2D: fv_xcd_remap {1, 0};

@@ -546,6 +546,8 @@ bool fv_small_eligible(const pb_batch *b);
 // kind 1 (Euler FD, halo 3): links between patches of one p >= 4, runs of
 // whole patches at least.
 std::vector<int4> column_runs(int kind, int K, const int *p, const int *nbr, int w, int cus, bool fit);
+// work-groups per CU of the library's own split of an FV batch
+int fv_own_per_cu(const pb_batch *b);
 // (re)builds the column-run tables for b->fv_column and b->fd_column (a
 // table is freed when its w is 0 or does not apply); host call, done when
 // the batch is created and when its tuning is set, never inside a capture

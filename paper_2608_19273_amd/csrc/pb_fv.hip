@@ -1234,6 +1234,17 @@ std::vector<int4> column_runs(int kind, int K, const int *p, const int *nbr, int
     return runs;
 }
 
+// Work-groups per CU of the library's own split: as many as make three waves
+// per SIMD (plane_waves), but two of single waves, whose runs get too short
+// (3072 patches of 8^3, us per step: 52.8 with twelve per CU, 40.4 with eight,
+// 44.4 with six; 1728 of 11^3 in FP32 with six, five, four of two waves 38, 42,
+// 41).
+int fv_own_per_cu(const pb_batch *b)
+{
+    const int waves = plane_waves(b);
+    return waves == 1 ? 8 : 12 / waves;
+}
+
 namespace {
 
 // w < 0: the library's own split, -w work-groups per CU
@@ -1281,12 +1292,7 @@ pb_status runs_prepare(pb_batch *b)
     // the batch exists, its steps are refused.)
     const bool own = b->fv_slab == 0 && b->fv_persist == 0 && b->fv_column == 0 && !b->fv_dma && !fv_small_eligible(b) &&
                      b->pde != PB_PDE_LINSYM && b->pmax <= kFvPmax;
-    // Fewer waves per work-group (plane_waves): as many as make three waves per
-    // SIMD, but two of single waves, whose runs get too short (3072 patches of
-    // 8^3, us per step: 52.8 with twelve per CU, 40.4 with eight, 44.4 with
-    // six; 1728 of 11^3 in FP32 with six, five, four of two waves 38, 42, 41).
-    const int waves = plane_waves(b), per_cu = waves == 1 ? 8 : 12 / waves;
-    pb_status st = build_table(b, b->fv_runs, 0, own ? -per_cu : b->fv_column, b->dim == 3);
+    pb_status st = build_table(b, b->fv_runs, 0, own ? -fv_own_per_cu(b) : b->fv_column, b->dim == 3);
     if (st != PB_OK) return st;
     const bool fd = b->dim == 3 && b->pde == PB_PDE_EULER;
     int w = b->fd_column;

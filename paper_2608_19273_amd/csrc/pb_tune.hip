@@ -67,7 +67,8 @@ pb_status apply(pb_batch *b, const pb_tuning &t)
     return runs_prepare(b);
 }
 
-std::vector<pb_tuning> candidates(const pb_batch *b, int kind)
+// (cus: compute units of the device)
+std::vector<pb_tuning> candidates(const pb_batch *b, int kind, int cus)
 {
     std::vector<pb_tuning> c;
     const pb_tuning base = current(b);
@@ -90,19 +91,39 @@ std::vector<pb_tuning> candidates(const pb_batch *b, int kind)
             t.fv_xcd_remap = remap;
             return t;
         };
-        if (b->dim == 3)
-            for (int w = 3; w >= 2; --w)
+        if (b->dim == 3) {
+            // Work-groups of four waves: column runs and the balanced schedule
+            // with the three that a CU holds, or two.  Of fewer waves a CU
+            // holds more (us per step of 3072 patches of 8^3, one wave each, with
+            // 3, 4, 6, 8 per CU: 63, 53, 47, 43; 1728 of 11^3, two waves: 68,
+            // 62, 73, 70; 2352 of 13^3, three waves: 149, 154, 152, 145).
+            const int own = fv_own_per_cu(b);
+            const int wide[2] = {own == 3 ? 3 : 8, own == 3 ? 2 : 4};
+            // The library's own split, where its runs are not those of a
+            // candidate below.
+            const auto same = [](const std::vector<int4> &x, const std::vector<int4> &y) {
+                return x.size() == y.size() && std::equal(x.begin(), x.end(), y.begin(), [](const int4 &p, const int4 &q) {
+                           return p.x == q.x && p.y == q.y && p.z == q.z;
+                       });
+            };
+            const auto runs = [&](int w, bool fit) {
+                return column_runs(0, b->K, b->p.data(), b->nbr.data(), w, cus, fit);
+            };
+            const std::vector<int4> mine = runs(own, true);
+            if (!same(mine, runs(wide[0], false)) && !same(mine, runs(wide[1], false)))
+                for (int remap = 1; remap >= 0; --remap) c.push_back(plain(remap));
+            for (int w : wide)
                 for (int remap = 1; remap >= 0; --remap) {
                     pb_tuning t = plain(remap);
                     t.fv_column = w;
                     c.push_back(t);
                 }
-        if (b->dim == 3 && b->uniform_p)
-            for (int remap = 1; remap >= 0; --remap) {
+            for (int remap = 1; remap >= 0 && b->uniform_p; --remap) {
                 pb_tuning t = plain(remap);
-                t.fv_persist = 3;
+                t.fv_persist = own;
                 c.push_back(t);
             }
+        }
         for (int remap = 1; remap >= 0; --remap)
             for (int s : slabs) {
                 pb_tuning t = plain(remap);
@@ -194,9 +215,6 @@ pb_status pb_autotune(pb_batch *b, int32_t kind, double cfl, double dt_fixed, do
     if (kind == 1 && (!std::isfinite(sigma_ko) || sigma_ko < 0.0)) { set_error("sigma_ko must be finite and >= 0"); return PB_EINVAL; }
     *out = pb_autotune_result{};
     const std::string key = tune_key(b, kind);
-    const std::vector<pb_tuning> cand = candidates(b, kind);
-    out->n_candidates = (int32_t)cand.size();
-    for (size_t i = 0; i < cand.size(); ++i) out->cand[i] = cand[i];
     if (use_cache) {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_cache.find(key);
@@ -208,6 +226,11 @@ pb_status pb_autotune(pb_batch *b, int32_t kind, double cfl, double dt_fixed, do
             return pb_batch_set_tuning(b, &it->second);
         }
     }
+    int cus = 0;
+    if (const pb_status sc = device_cus(&cus); sc != PB_OK) return sc;
+    const std::vector<pb_tuning> cand = candidates(b, kind, cus);
+    out->n_candidates = (int32_t)cand.size();
+    for (size_t i = 0; i < cand.size(); ++i) out->cand[i] = cand[i];
     if (kind == 1 && b->pde == PB_PDE_LINSYM) {
         pb_status st = fd_prepare(b);
         if (st != PB_OK) return st;
