@@ -207,6 +207,11 @@ pb_status pb_autotune(pb_batch *b, int32_t kind, double cfl, double dt_fixed, do
         set_error("pb_autotune: FD tuning applies to the linear system and to Euler");
         return PB_EINVAL;
     }
+    // (the trials are the stage kernels, which read FP64 patches of p^3 cells)
+    if (kind == 1 && b->pde == PB_PDE_LINSYM && (b->dim != 3 || b->storage != PB_STORE_FP64)) {
+        set_error("pb_autotune: the linear system's FD step needs dim 3 and FP64 storage");
+        return PB_EUNSUPPORTED;
+    }
     if (kind == 1 && b->pde == PB_PDE_EULER &&
         (b->dim != 3 || b->storage != PB_STORE_FP64 || b->pmax > kFvPmax || b->h < 3)) {
         set_error("pb_autotune: the Euler FD step needs dim 3, FP64 storage, p <= 16 and a halo of 3");
