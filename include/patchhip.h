@@ -370,8 +370,11 @@ pb_status pb_stream_copy(const void *src, void *dst, size_t bytes, void *stream)
 /* --------------------------------------------------------------- tuning -- */
 
 /* Launch-shape choices of the step kernels.  None of them changes what is
- * computed; the FV slab changes the order of a few additions at slab seams
- * (last-bit differences), the others change nothing in the results. */
+ * computed, and none but fv_dma = 1 and fd_ws = 2 (equal to roundoff) changes a
+ * bit of the results: a patch's new state depends on its own and its neighbours'
+ * values and dt, not on how the batch is dealt to work-groups, on the other
+ * patches of the batch (as long as it takes the same kernel: patches of one p
+ * with p^3 <= 256 have their own) or on the device's number of compute units. */
 typedef struct {
     int32_t fv_slab;          /* FV: z-planes per work-group.  0 = the library's
                                  own split (column runs as for fv_column, no
@@ -412,9 +415,7 @@ typedef struct {
                                  than the work-groups a CU holds at once there
                                  is no partly filled last round; fv_slab is
                                  then unused.  0 = off (fv_slab), the
-                                 default.  Results differ from
-                                 slab mode only where a slab seam changes the
-                                 order of additions. */
+                                 default. */
     int32_t fv_column;        /* FV 3D (register kernel): w in 1..8 = column
                                  runs: the patches are linked along +z (k to
                                  its +z neighbour s where s's -z neighbour is
@@ -433,9 +434,7 @@ typedef struct {
                                  precedence over
                                  fv_persist and fv_slab; builds a small device
                                  table here (host call, PB_EHIP if that
-                                 fails).  0 = off, the default.  Results
-                                 differ from slab mode only where a run
-                                 starts inside a patch, as at a slab seam. */
+                                 fails).  0 = off, the default. */
     int32_t fd_column;        /* Euler FD (plane kernel): w in 1..8 = column
                                  runs as for fv_column (links between patches
                                  of one p >= 4; every run at least one whole

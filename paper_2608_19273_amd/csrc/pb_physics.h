@@ -155,7 +155,9 @@ struct AdvVar {
 
 // Compressible Euler, ideal gas: Q = (rho, m, E), p = (gamma-1)(E - |m|^2/(2 rho)),
 // F_d = (m_d, m_d m/rho + p e_d, (E + p) m_d/rho), speed |m_d/rho| + sqrt(gamma p/rho).
-// aux = (1/rho, p, c).
+// aux = (1/rho, p, c).  The squares are added by named fused operations: which
+// of two products the compiler fuses would depend on the code around a copy of
+// this function, and a cell's pressure must not.
 template <int DIM>
 struct Euler {
     static constexpr int N = DIM + 2, A = 3, E = 0, M = 0, DIMS = DIM;
@@ -164,8 +166,8 @@ struct Euler {
     __device__ __forceinline__ void aux(const double *q, const double *, double *a) const
     {
         const double ir = 1.0 / q[0];
-        double m2 = q[1] * q[1] + q[2] * q[2];
-        if (DIM == 3) m2 += q[3] * q[3];
+        double m2 = fma(q[2], q[2], q[1] * q[1]);
+        if (DIM == 3) m2 = fma(q[3], q[3], m2);
         const double p = (gamma - 1.0) * (q[DIM + 1] - 0.5 * m2 * ir);
         a[0] = ir;
         a[1] = p;
@@ -174,8 +176,8 @@ struct Euler {
     __device__ __forceinline__ void aux_fast(const double *q, const double *, double *a) const
     {
         const double ir = recip(q[0]);
-        double m2 = q[1] * q[1] + q[2] * q[2];
-        if (DIM == 3) m2 += q[3] * q[3];
+        double m2 = fma(q[2], q[2], q[1] * q[1]);
+        if (DIM == 3) m2 = fma(q[3], q[3], m2);
         const double p = (gamma - 1.0) * (q[DIM + 1] - 0.5 * m2 * ir);
         a[0] = ir;
         a[1] = p;
