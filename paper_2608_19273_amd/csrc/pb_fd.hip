@@ -323,8 +323,9 @@ __global__ __launch_bounds__(kFdThreads, 2) void fd_stage_kernel(
         }
         // 4. stage update in the output layout, in two rounds of two column
         //    tiles: all reads of a round first (one memory round trip), then
-        //    the arithmetic and the stores
-        {
+        //    the arithmetic and the stores (rows beyond the last unknown read
+        //    the first; a wave of nothing else is left out)
+        if (16 * w < N) {
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 long long gbase[2];
@@ -885,11 +886,15 @@ __global__ __launch_bounds__(64) void fd_stage_tile_kernel(
             for (int nt = 0; nt < 4; ++nt) am[c / 4][nt][c % 4] += ko[nt];
         }
         buf ^= 1;   // the next tile's first chunk goes to the other buffer
-        // stage update, one row tile at a time (all loads of a round first)
+        // stage update, one row tile at a time (all loads of a round first);
+        // tiles beyond the last unknown are left out (160 patches of 16^3, us
+        // per step with their loads of the first unknown and without: 4 unknowns
+        // 404 and 264, 24 unknowns 1178 and 1100)
         const long long C = (long long)p * p * p, pp = (long long)p * p;
         const long long cell = ((long long)W.tz * p + (W.ty + yy)) * p + (W.tx + x);
 #pragma unroll
         for (int rt = 0; rt < 4; ++rt) {
+            if (16 * rt >= N) break;
             double bv[4][4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
