@@ -1315,7 +1315,9 @@ pb_status runs_prepare(pb_batch *b)
                      b->pde != PB_PDE_LINSYM && b->pmax <= kFvPmax;
     pb_status st = build_table(b, b->fv_runs, 0, own ? -fv_own_per_cu(b) : b->fv_column, b->dim == 3);
     if (st != PB_OK) return st;
-    const bool fd = b->dim == 3 && b->pde == PB_PDE_EULER;
+    // (no FD table for a batch whose FD steps are refused: most of them have a
+    // halo of 1; creating 2048 patches of 16^3 takes 0.1 ms less)
+    const bool fd = b->dim == 3 && b->pde == PB_PDE_EULER && b->h >= 3 && b->storage == PB_STORE_FP64;
     int w = b->fd_column;
     if (fd && w == 2 && b->pmax <= kFvPmax) {
         // the default: runs shorter than a patch where the batch has fewer
