@@ -1433,10 +1433,14 @@ pb_status launch_fd_stage(pb_batch *b, int stage, int rk_stages, const void *q0_
         launch_main(b, fd_stage_tile_kernel, dim3(grid), dim3(64), 0, s, y, q0, y1, y2, out, tiles, b->fd_n_items,
                     b->d_fd_A, b->N, fin, ca, sigma, b->fd_xcd_remap);
     } else if (b->fd_ws && b->fd_n_items > cus && b->fd_n_boxes > 0) {
-        // boxes, two work-groups per CU.  Up to one 4x4x4 tile per CU the
-        // wave-specialised kernel is the faster (58 unknowns, 256 tiles: 22
-        // against 27 us per stage), beyond it needs a second round (384
-        // tiles: 36 against 28 us; 4096 patches: 4.8 against 3.4 ms)
+        // boxes, two work-groups per CU.  Above one 4x4x4 tile per CU the
+        // wave-specialised kernel needs a second round and the boxes are faster
+        // for every number of unknowns; up to there it is the faster from 24
+        // unknowns on.  us per stage, wave-specialised and boxes, on 256 CUs:
+        // 256 tiles of 16^3 patches 5.7 and 5.6 (1 unknown), 6.7 and 6.6 (8), 11.8
+        // and 11.8 (24), 16.4 and 19.0 (40), 21.3 and 26.1 (58), of 4^3 patches
+        // 9.8 and 11.3 (24), 19.4 and 26.8 (58); 320 tiles 7.4 and 5.7, 8.8 and
+        // 6.8, 17.2 and 12.1, 25.7 and 19.1, 35.6 and 26.5.
         const int grid = std::max(1, std::min(b->fd_n_boxes, 2 * cus));
         auto go = [&](auto kern) {
             launch_main(b, kern, dim3(grid), dim3(kBoxThreads), 0, s, y, q0, y1, y2, out,
