@@ -275,6 +275,12 @@ def bench_config0(torch, pb, I, calls):
     return out
 
 
+# State-sized arrays that the four stages of an RK4 step read and write: stage 1
+# reads Q^n and writes y1, stages 2 and 3 read the stage value and Q^n and write
+# the next one, stage 4 reads Q^n, y1, y2 and y3 and writes Q^{n+1}: 2 + 3 + 3 + 5.
+RK4_ARRAYS = 13
+
+
 def bench_fd(torch, pb, I, steps, warmup):
     log("config-2 IC (4096 patches, 58 unknowns)")
     b = I.config2()
@@ -297,7 +303,7 @@ def bench_fd(torch, pb, I, steps, warmup):
     N = b.n_unknowns
     # per RK4 step: 4 x (3 dense N x N products + 3 D4 (4 flop) + 3 KO6 (9 flop) + update) per unknown
     flop_cell = 4 * (3 * 2 * N * N + N * (3 * 4 + 3 * 9 + 4))
-    bytes_cell = 16 * N * 8
+    bytes_cell = RK4_ARRAYS * N * 8
     step_kernel_s = kern_ms / 1e3 / max(launches, 1) * 4
     return {"workload": "linear symmetric system N=58, 4096 patches {4^3,8^3,16^3} 1:2:1 shuffled "
                         f"({cells} cells), FD4 + KO6 (sigma 0.1) + RK4, CFL 0.5, FP64",
@@ -324,11 +330,7 @@ def bench_fd_euler(torch, pb, I, steps, warmup):
     st = B.stats()
     B.close()
     N = b.n_unknowns
-    # per RK4 step, state-sized arrays in + out: stage 1 reads Q^n, writes the
-    # next stage value and the running sum; stages 2-3 read the stage value,
-    # Q^n and the sum, write two; stage 4 reads the stage value and the sum,
-    # writes Q^{n+1}: (1+2) + (3+2) + (3+2) + (2+1) = 16 arrays of N doubles
-    bytes_cell = 16 * N * 8
+    bytes_cell = RK4_ARRAYS * N * 8
     step_kernel_s = kern_ms / 1e3 / max(launches, 1) * 4
     return {"workload": "3D Euler, FD4 + KO6 (sigma 0.1) + RK4, CFL 0.5, 2048 patches of 16^3 "
                         f"({cells} cells) joined by face neighbours, halo 3, FP64, seeded Fourier-mode IC",
