@@ -216,7 +216,11 @@ struct Srhd {
     // the primitives feed the fluxes of the step and the speeds its dt.
     // c_s and the root over it are taken together, sqrt(c_s^2 (1 - v^2) (...)):
     // four roots instead of five, three of them independent (2048 patches of
-    // 16^3: con2prim pass 127 -> 125 us, step 188 -> 184).
+    // 16^3: con2prim pass 127 -> 125 us, step 188 -> 184).  Error of the new
+    // state (2-norm) against long double over 16 drawn states of 8 patches, with
+    // five roots and with four: after one step 5.92e-16 and 5.93e-16 (ratio
+    // 1.0025 +- 0.0012), after ten 2.12e-16 and 2.09e-16 (0.991 +- 0.012); of dt
+    // 9.7e-17 and 9.1e-17 rms.
     __device__ __forceinline__ void aux(const double *q, const double *e, double *a) const
     {
         const double p = e[0];
