@@ -136,11 +136,12 @@ __device__ __forceinline__ double stage_dt(Ctrl *ctrl, int slot, double dt_fixed
 //   S = 2: out = q0 + dt R
 //   S = 3: out = rk_base(q0, y1, y2, y) + dt/6 R
 //   S = 4: out = y + dt R            (y = Q^n)
-// Bound: issue at 2 waves per SIMD in stages 0-2 (256 to 277 us on 2048 16^3
-// patches; they move 2 and 3 arrays of 336 MB, 106 and 160 us at the copy
-// rate), memory in stage 3 (350 us for 5 arrays and the halo strips).  With a
-// running sum of the k the stages moved 3, 5, 5 and 3 arrays in 291, 342, 346
-// and 298 us.
+// Bound on 2048 16^3 patches: the chain of a plane at 2 waves per SIMD in stage
+// 0 (212 us for 0.76 GB, 121 us at the copy rate; vector unit busy 34 %, LDS
+// 65 %), memory more and more after it (stages 1 and 2 230 us for 1.10 GB, 75 %
+// of the copy rate; stage 3 318 us for 1.78 GB, 89 %).  With a running sum of
+// the k the stages moved 3, 5, 5 and 3 arrays in 291, 342, 346 and 298 us
+// where these took 256, 277, 277 and 350 (a slower box).
 // The final stages (3 and 4) fold the speeds of the new state into the
 // hand-over to the next step (FvChain), with a fixed dt too, where nobody reads
 // them: without that code the compiler
@@ -637,8 +638,9 @@ __global__ __launch_bounds__(kFvThreads) void fd_euler_small_kernel(
 // from group to group with the next group's cells in flight.  The state is
 // read and written once per step, against 13 passes and four launches.
 // The arithmetic is the small-patch stage kernel's.
-// Bound: FP64 issue.  1024 patches of 6^3: 25 us per step, against four
-// stages of 15 us.
+// Bound: LDS, which is busy 75 % of the time, a quarter of that with bank
+// conflicts (vector unit 44 %).  1024 patches of 6^3: 25 us per step, against
+// four stages of 15 us.
 constexpr int kSelfPerCu = 3;   // work-groups resident at once (by registers)
 
 template <int STAGES>

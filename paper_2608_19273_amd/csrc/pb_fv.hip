@@ -750,9 +750,10 @@ __global__ __launch_bounds__(kFvThreads, 2) void fv_step_dma_kernel(
 // the same patch in LDS: nothing is loaded or evaluated twice.  With one p the
 // patches lie one after the other, so the group gives every address but the
 // neighbours' indexes, which are loaded two groups ahead.
-// Bound: FP64 issue.  8694 patches of 6^3 (1.9 M cells, 150 MB): 36 us per
-// step with kSelf, 54 us (8000 of them) without, 24 us at the copy rate; one group per
-// work-group, halo cells loaded and evaluated in every case: 62 us.
+// Bound: vector issue and LDS, each busy 60 % of the time between the barriers.
+// 8694 patches of 6^3 (1.9 M cells, 150 MB): 36 us per step with kSelf, 54 us
+// (8000 of them) without, 24 us at the copy rate; one group per work-group, halo
+// cells loaded and evaluated in every case: 62 us.
 constexpr int kSmallHalo = 2;   // halo cells per thread, at most
 
 // doubles per LDS slot: Q and aux of one cell side by side, so that a
