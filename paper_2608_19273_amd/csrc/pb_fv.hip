@@ -1194,6 +1194,11 @@ pb_status dispatch(pb_batch *b, F &&f)
 // The library's own split (`fit`; no tuning asks for another) gives a chain
 // its share rounded down, so that all runs are resident at once, and lets the
 // FD runs be shorter than a patch where whole patches leave CUs without work.
+// Independent patches between half and all of the resident work-groups thus get
+// one run each.  Ten steps of 16^3 patches with one run each and with two, us:
+// 400 patches 436 and 455, 512 439 and 471, 600 570 and 541, 700 592 and 616, 767
+// 621 and 655 (384: 424 and 363, and two is what they get); 13^3 520 392 and 406,
+// 1000 532 and 644; 8^3 1030 217 and 193, 1500 260 and 278, 2000 302 and 325.
 std::vector<int4> column_runs(int kind, int K, const int *p, const int *nbr, int w, int cus, bool fit)
 {
     const int pmin = kind == 0 ? 2 : 4;
